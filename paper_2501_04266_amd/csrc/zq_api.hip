@@ -15,10 +15,6 @@
 #include "zq_host.h"
 #include "zq_internal.h"
 
-#ifndef ZQ_FIXED
-#define ZQ_FIXED 1
-#endif
-
 namespace {
 
 using namespace zq;
@@ -76,6 +72,27 @@ int dequantize(const void* codes, const float* scales, int64_t n, int32_t block,
                 scales, n, lgB, y);
 }
 
+// One launch for a whole level: the vector kernel over groups of 4 wave tiles
+// of full blocks (the last group moved back to end with them) and one more
+// workgroup for a short last block; a level smaller than one group runs one
+// wave per block.  Levels with few E = 32 waves take E = 8, where a block may
+// span at most one wave.
+template <typename Src>
+int launch_reduce(const Src& src, int P, int64_t m, int32_t block, int lgB, uint8_t* packed_out, float* scales_out,
+                  void* y, int yt, hipStream_t st) {
+  const int64_t nfull = m / block, rest = m - nfull * block;
+  const int64_t waves_large = (nfull + 64 / (block / kReduceElems) - 1) / (64 / (block / kReduceElems));
+  const bool small = block <= 512 && waves_large < ZQ_REDUCE_SMALL_WAVES;
+  const int64_t group = kThreads / 64 * (64 / (block / (small ? kReduceElemsSmall : kReduceElems)));
+  if (nfull < group)
+    return launch(reduce_blocks_kernel<Src>(lgB), (unsigned)num_scales(m, block), 64u, st, src, P, m, packed_out,
+                  scales_out, y, yt);
+  const int64_t grid = grid_for(nfull, group * reduce_groups(P, block, small));
+  if (grid == 0 || grid + (rest > 0) > kMaxGrid) return ZQ_E_SIZE;
+  return launch(reduce_kernel<Src>(lgB, P, small, yt), (unsigned)(grid + (rest > 0)), kThreads, st, src, P, nfull,
+                (int)rest, rest > 0 ? (unsigned)grid : ~0u, packed_out, scales_out, y);
+}
+
 // Shared body of qgz_reduce_level (fused = false: INT4 output only, both
 // pointers required) and qgz_reduce_dequantize (fused = true: y of dtype yt
 // required, the INT4 output optional -- both of its pointers or neither).
@@ -113,53 +130,14 @@ int reduce(const uint8_t* packed_in, const float* scales_in, int32_t P, int64_t 
       if (overlap(outs[o], outs[o2])) return ZQ_E_ALIAS;
   }
 
-  // every slice starts 16-byte aligned when m % 32 == 0: vector path over
-  // whole groups of blocks (4 wave tiles of 64 lanes x E elements each)
-  const bool vector_path = m % 32 == 0;
-  const int64_t full_blocks = vector_path ? m / block : 0;
-  const int64_t waves_large = (full_blocks + 64 / (block / kReduceElems) - 1) / (64 / (block / kReduceElems));
-  ReduceShape shape = ReduceShape::kLarge;
-  if (block <= 512 && waves_large < ZQ_REDUCE_SMALL_WAVES) shape = ReduceShape::kSmall;
-  else if (block <= 512 && P <= 2 && !fused) shape = ReduceShape::kTwoSlices;
-  const int64_t group_blocks = kThreads / 64 * (64 / (block / reduce_elems(shape)));
-  const int64_t groups = full_blocks / group_blocks;
-  const int64_t nfull = groups * group_blocks;
-  const int64_t grid = grid_for(groups, reduce_tiles(shape));
-  if (grid == 0 && groups > 0) return ZQ_E_SIZE;
-
-  // P = 2, 4, 8 on large levels: the kernel with the slice count fixed at
-  // compile time (each workgroup takes reduce_fixed_tiles(P) groups)
-  // and on small levels (one group per workgroup, the small-level group size)
-  const bool small = shape == ReduceShape::kSmall;
-  ReduceKernel fixed = !ZQ_FIXED ? nullptr
-                       : small   ? reduce_fixed_small_kernel(lgB, P, fused ? yt : -1, gather)
-                                 : reduce_fixed_kernel(lgB, P, fused ? yt : -1, gather);
-  // (its groups: the same whole-group range [0, nfull) in its own group size)
-  const int64_t fixed_groups =
-      !fixed ? 0 : small ? groups : nfull / (kThreads / 64 * (64 / (block / reduce_fixed_elems())));
-  const int64_t fixed_grid = !fixed ? 0 : small ? groups : grid_for(fixed_groups, reduce_fixed_tiles(P));
-  if (fixed && fixed_grid == 0 && groups > 0) return ZQ_E_SIZE;
-
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (groups > 0) {
-    int rc = fixed ? launch(fixed, (unsigned)fixed_grid, kThreads, st, packed_in, scales_in, (int)P, slice_bytes, nb,
-                            nfull, packed_out, scales_out, y)
-                   : launch(gather ? reduce_gather_kernel(lgB, shape) : reduce_kernel(lgB, shape, fused ? yt : -1),
-                            (unsigned)grid, kThreads, st, packed_in, scales_in, (int)P, slice_bytes, nb, nfull,
-                            packed_out, scales_out, y);
-    if (rc != ZQ_OK) return rc;
-  }
-  // remaining blocks (those after the last whole group, including a short
-  // last block, or all of them when slices are not 16-byte aligned): one wave
-  // per block
-  for (int64_t b0 = nfull; b0 < nb; b0 += (1LL << 30)) {
-    const int64_t cnt = (nb - b0) < (1LL << 30) ? (nb - b0) : (1LL << 30);
-    int rc = launch(reduce_generic_kernel(gather), (unsigned)cnt, 64u, st, packed_in, scales_in, (int)P, slice_bytes,
-                    nb, m,
-                    (int)block, b0, packed_out, scales_out, fused ? y : nullptr, fused ? yt : 0);
-    if (rc != ZQ_OK) return rc;
-  }
-  return ZQ_OK;
+  const int yk = fused ? yt : -1;
+  if (gather)
+    return launch_reduce(SlicesInTable{reinterpret_cast<const uint8_t* const*>(packed_in),
+                                       reinterpret_cast<const float* const*>(scales_in)},
+                         P, m, block, lgB, packed_out, scales_out, y, yk, st);
+  return launch_reduce(SlicesInRow{packed_in, scales_in, slice_bytes, nb}, P, m, block, lgB, packed_out, scales_out, y,
+                       yk, st);
 }
 
 // Slice-address tables of qgz_reduce_level_gather_noalloc: one static array

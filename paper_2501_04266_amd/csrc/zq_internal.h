@@ -1,6 +1,7 @@
 // zq_internal.h -- launch geometry and kernel handles shared by the kernel and
 // API translation units.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace zq {
@@ -64,24 +65,6 @@ constexpr int deq4_elems(int out_bytes) { return out_bytes == 4 ? ZQ_DEQ4_E_F32 
 #endif
 constexpr int kReduceElems = ZQ_REDUCE_E;  // 16 bytes of every slice per lane
 constexpr int kReduceElemsSmall = 8;  // 4 bytes per slice per lane, for small levels
-// Launch shapes of the reduce level (see the kernel): 32 elements per lane
-// and 4-slice batches; the same with 2-slice batches for P <= 2; 8 elements
-// per lane and 16-slice batches for levels with few waves.  TR = groups of 4
-// wave tiles per workgroup, processed as one pipelined sequence.
-#ifndef ZQ_REDUCE_TR
-#define ZQ_REDUCE_TR 1
-#endif
-#ifndef ZQ_REDUCE_TR2
-#define ZQ_REDUCE_TR2 2
-#endif
-#ifndef ZQ_REDUCE_TR_SMALL
-#define ZQ_REDUCE_TR_SMALL 1
-#endif
-enum class ReduceShape { kLarge, kTwoSlices, kSmall };
-constexpr int reduce_elems(ReduceShape s) { return s == ReduceShape::kSmall ? kReduceElemsSmall : kReduceElems; }
-constexpr int reduce_tiles(ReduceShape s) {
-  return s == ReduceShape::kTwoSlices ? ZQ_REDUCE_TR2 : s == ReduceShape::kSmall ? ZQ_REDUCE_TR_SMALL : ZQ_REDUCE_TR;
-}
 // A level whose E = 32 launch would have fewer waves than this runs the small
 // variant (4x the waves, more slices in flight per wave).
 #ifndef ZQ_REDUCE_SMALL_WAVES
@@ -91,25 +74,55 @@ constexpr int reduce_tiles(ReduceShape s) {
 // (x, full blocks, out, scales, length of the short last block or 0)
 using QuantKernel = void (*)(const void*, int64_t, uint8_t*, float*, int);
 using DequantKernel = void (*)(const uint8_t*, const float*, int64_t, int, void*);
-using ReduceKernel = void (*)(const uint8_t*, const float*, int, int64_t, int64_t, int64_t, uint8_t*, float*, void*);
-using ReduceGenericKernel = void (*)(const uint8_t*, const float*, int, int64_t, int64_t, int64_t, int, int64_t,
-                                     uint8_t*, float*, void*, int);
+
+// Where the P slices of a reduce level are: back to back from one address each
+// for bytes and scales, or at the addresses that two device tables hold (the
+// peers' buffers mapped into this GPU's address space).
+struct SlicesInRow {
+  const uint8_t* in;
+  const float* sin;
+  int64_t slice_bytes, slice_scales;
+  __device__ const uint8_t* bytes(int p) const { return in + p * slice_bytes; }
+  __device__ const float* scales(int p) const { return sin + p * slice_scales; }
+};
+struct SlicesInTable {
+  const uint8_t* const* in;
+  const float* const* sin;
+  __device__ const uint8_t* bytes(int p) const { return in[p]; }
+  __device__ const float* scales(int p) const { return sin[p]; }
+};
+// (slices, P, full blocks, length of the short last block and the workgroup that
+// takes it (past the grid when there is none), out, scales, y)
+template <typename Src>
+using ReduceKernel = void (*)(Src, int, int64_t, int, unsigned, uint8_t*, float*, void*);
+// (slices, P, m, out, scales, y, dtype of y or -1)
+template <typename Src>
+using ReduceBlocksKernel = void (*)(Src, int, int64_t, uint8_t*, float*, void*, int);
 
 QuantKernel quant_kernel(int dt, int qbits, int lgB);
 DequantKernel dequant_kernel(int dt, int qbits);
+// Groups per workgroup of the kernel of a level (its launch covers the full
+// blocks in groups of 4 wave tiles): four on large levels of two slices, else
+// one.
+constexpr int fixed_groups(int P) { return P == 2 ? 4 : 1; }
+constexpr int reduce_groups(int P, int block, bool small) {
+  return !small && block >= 64 && block <= 256 ? fixed_groups(P) : 1;
+}
 // ydt < 0: INT4 output only; otherwise also the fused dequantisation to ydt
-ReduceKernel reduce_kernel(int lgB, ReduceShape shape, int ydt);
-// slices through device tables of P pointers (bytes, scales); INT4 output only
-ReduceKernel reduce_gather_kernel(int lgB, ReduceShape shape);
-ReduceGenericKernel reduce_generic_kernel(bool gather);
-// vector-path kernel with the slice count fixed at compile time, for P = 2, 4
-// or 8 and B = 64, 128 or 256 (ydt < 0: INT4 output only; gather: slices
-// through pointer tables, INT4 output only); null where there is none.  Each
-// workgroup takes reduce_fixed_tiles(P) groups.
-ReduceKernel reduce_fixed_kernel(int lgB, int P, int ydt, bool gather);
-// The same for small levels (the small-level lane width, one group per
-// workgroup), P = 2, 4, 8; null otherwise.
-ReduceKernel reduce_fixed_small_kernel(int lgB, int P, int ydt, bool gather);
+// (slices in a row only)
+template <typename Src>
+ReduceKernel<Src> reduce_kernel(int lgB, int P, bool small, int ydt);
+// one wave per block, for levels smaller than one group
+template <typename Src>
+ReduceBlocksKernel<Src> reduce_blocks_kernel(int lgB);
+template <>
+ReduceKernel<SlicesInRow> reduce_kernel(int lgB, int P, bool small, int ydt);
+template <>
+ReduceKernel<SlicesInTable> reduce_kernel(int lgB, int P, bool small, int ydt);
+template <>
+ReduceBlocksKernel<SlicesInRow> reduce_blocks_kernel(int lgB);
+template <>
+ReduceBlocksKernel<SlicesInTable> reduce_blocks_kernel(int lgB);
 // a chunk of 64-bit table entries passed by value to the table-fill kernel
 constexpr int kTableChunk = 64;
 struct TableChunk {
@@ -117,7 +130,5 @@ struct TableChunk {
 };
 using FillTableKernel = void (*)(uint64_t*, TableChunk, int);
 FillTableKernel fill_table_kernel();
-int reduce_fixed_tiles(int P);
-int reduce_fixed_elems();  // elements per lane of that kernel
 
 }  // namespace zq

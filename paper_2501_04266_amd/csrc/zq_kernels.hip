@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "zq.h"
 #include "zq_device.h"
 #include "zq_internal.h"
@@ -42,9 +44,6 @@
 // other waves' arithmetic, then back to normal for the wave's own arithmetic.
 #ifndef ZQ_PRIO_QUANT
 #define ZQ_PRIO_QUANT 1
-#endif
-#ifndef ZQ_PRIO_REDUCE
-#define ZQ_PRIO_REDUCE 0
 #endif
 #ifndef ZQ_PRIO_DEQ
 #define ZQ_PRIO_DEQ 0
@@ -81,24 +80,6 @@ __device__ __forceinline__ void prio_compute() {
 #ifndef ZQ_NT_SCALES
 #define ZQ_NT_SCALES 0
 #endif
-// slices loaded ahead per batch in the reduce level (large / small levels)
-#ifndef ZQ_REDUCE_U
-#define ZQ_REDUCE_U 4
-#endif
-#ifndef ZQ_REDUCE_U_SMALL
-#define ZQ_REDUCE_U_SMALL 16
-#endif
-// batch pipelining (see the reduce kernel) per launch shape: large / P <= 2 / small
-#ifndef ZQ_REDUCE_PIPE
-#define ZQ_REDUCE_PIPE 1
-#endif
-#ifndef ZQ_REDUCE_PIPE2
-#define ZQ_REDUCE_PIPE2 1
-#endif
-#ifndef ZQ_REDUCE_PIPE_SMALL
-#define ZQ_REDUCE_PIPE_SMALL 0
-#endif
-
 namespace zq {
 namespace {
 
@@ -517,29 +498,36 @@ __global__ void __launch_bounds__(kDeqThreads) k_dequant(const uint8_t* __restri
 }
 
 // ------------------------------------------------------------------ reduce level
-// Vector path: slices 16-byte aligned (m % 32 == 0), blocks [0, nfull) with
-// nfull a multiple of the group size GB below.  A lane owns E consecutive
-// elements (E/2 bytes of every slice: consecutive lanes read consecutive
-// bytes); L = B/E lanes hold one block; a wave tile is 64 lanes = BPW blocks.
-// The 4 waves of a workgroup take 4 adjacent tiles (a group of GB blocks) and
-// workgroup g processes groups g*TR .. g*TR + TR - 1.  Every load and store is
-// addressed from a wave-uniform base plus the lane's offset, with no
-// predicates.  Large levels use E = 32 (16 B per slice per lane), small levels
-// (few waves, often many slices) E = 8, so that four times as many waves run.
+// Vector path: the full blocks [0, nfull), nfull >= the group size GB below.
+// A lane owns E consecutive elements (E/2 bytes of every slice: consecutive
+// lanes read consecutive bytes); L = B/E lanes hold one block; a wave tile is
+// 64 lanes = BPW blocks.  The 4 waves of a workgroup take 4 adjacent tiles (a
+// group of GB blocks).  Every load and store is addressed from a wave-uniform
+// base plus the lane's offset, with no predicates: where GB does not divide
+// nfull the last group is moved back to end at nfull and recomputes some of
+// its neighbour's blocks, rewriting identical values.  Large levels use E = 32
+// (16 B per slice per lane), small levels (few waves, often many slices)
+// E = 8, so that four times as many waves run.
 //
-// Slices are loaded U at a time (a batch).  With PIPE the batches of a
-// workgroup's groups form one sequence of jobs whose register buffers
-// alternate, so the loads of the next batch -- of this tile or of the next
-// group -- are in flight while the current one is summed or the tile
-// requantised; without it each batch is loaded, then summed.
+// Slices start where ceil(m/2) puts them, at any byte address when m % 32 is
+// not 0, so slice words are loaded through types of alignment 1 (one
+// global_load_dwordx4 all the same: the gfx9 ABI runs with unaligned global
+// access on); outputs are always aligned.  A short last block (tail elements)
+// is reduced by the first wave of one more workgroup of the same launch.
+// Bound by HBM and, at few waves, by latency.  One launch over all of an odd
+// level (P = 8, m = 15,432,099, B = 64: 17 us, 4.6 TB/s) replaced a wave per
+// block with byte loads (171 us); the blocks after the last whole group used to
+// take such waves too, one slice after the other (P = 64, m = 1,000,000,
+// B = 256: 36.6 -> 14.1 us).
 //
 // Per slice and element: one v_cvt_off_f32_i4 (q/16), one multiply by 16*s
 // ((q/16)*(16 s) is the exact real q*s, so the rounded product is fl(q*s)),
 // one add.  16*s is exact unless it overflows (s > 2^123, i.e. inputs above
-// ~7e37); a wave holding such a scale multiplies by 16 first instead.  The
-// first slice initialises the sum with its product: +0 + x = x for every x
-// but -0, and a -0 sum and a +0 sum requantise to the same code and scale.
-// Slices are summed in ascending order, exactly as defined.
+// ~7e37); a wave holding such a scale multiplies by 16 first instead.  In the
+// fixed-P kernel the first slice initialises the sum with its product:
+// +0 + x = x for every x but -0, and a -0 sum and a +0 sum requantise to the
+// same code and scale.  Slices are summed in ascending order, exactly as
+// defined.
 //
 // YDT >= 0 adds the fused final dequantisation: the requantised codes are
 // turned back into fl(code * s_out) in YDT (the value qgz_dequantize would
@@ -548,9 +536,55 @@ __global__ void __launch_bounds__(kDeqThreads) k_dequant(const uint8_t* __restri
 // bytes per lane are staged in LDS and written as workgroup-contiguous
 // 16-byte stores, as in the dequantiser.
 
+// A wave-uniform value, held in scalar registers from here on.
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// The words at a wave-uniform address plus a lane's byte offset, from any byte
+// address: one global load whose 64-bit part is in scalar registers.  (The
+// builtin has to see the unaligned type, and the address space, which the
+// conversion to scalar registers hides from the compiler.)
+#define ZQ_GLOBAL __attribute__((address_space(1)))
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+template <int NW>
+__device__ __forceinline__ void load_words_any(const void* base, uint32_t lane_byte, uint32_t (&w)[NW]) {
+  static_assert(ZQ_NT_REDUCE & 1, "nontemporal loads");
+  const ZQ_GLOBAL char* p =
+      reinterpret_cast<const ZQ_GLOBAL char*>(uniform((int64_t)reinterpret_cast<uintptr_t>(base))) + lane_byte;
+  if constexpr (NW == 4) {
+    const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32x4_any*>(p));
+    w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+  } else if constexpr (NW == 2) {
+    const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32x2_any*>(p));
+    w[0] = t.x; w[1] = t.y;
+  } else {
+    static_assert(NW == 1, "words");
+    w[0] = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32_any*>(p));
+  }
+}
+
+// A slice's words and scale for one wave tile.
+template <int NW>
+__device__ __forceinline__ void load_slice(const uint8_t* bytes, uint32_t lane_byte, const float* scales,
+                                           uint32_t lane_scale, uint32_t (&w)[NW], float& s) {
+  uint32_t sw[1];
+  load_words_any(bytes, lane_byte, w);
+  load_words_any(scales, 4 * lane_scale, sw);
+  s = u2f(sw[0]);
+}
+
 // One slice into a lane's sum: acc[k] = fl(acc[k] + fl(q_k * s)) for the E
-// codes of the NW words ww (FIRST: acc[k] = fl(q_k * s)).
-template <int E, int NW, bool FIRST>
+// codes of the NW words ww (FIRST: acc[k] = fl(q_k * s)).  KEEP: an empty asm keeps
+// each sum in its branch: the compiler otherwise moves the additions, common
+// to both branches, behind them and behind the following slices, and holds the
+// products of all slices of a batch in registers meanwhile (the any-P kernel:
+// 315 registers, one wave per SIMD, against 125 and four).
+template <int E, int NW, bool FIRST, bool KEEP = false>
 __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[NW], float sc) {
   const float s16 = sc * 16.0f;
   if (__all(s16 <= kMaxFloat)) {  // wave-uniform: 16*s exact for every lane
@@ -562,6 +596,7 @@ __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[
       for (int k = 0; k < 8; ++k) {
         const float prod = f[k] * s16;
         acc[8 * j + k] = FIRST ? prod : acc[8 * j + k] + prod;
+        if constexpr (KEEP) asm volatile("" : "+v"(acc[8 * j + k]));
       }
     }
   } else {
@@ -578,16 +613,16 @@ __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[
   }
 }
 
-// Requantise one wave tile (blocks from blk0, group grp) and store its INT4
-// codes and scales (when out is not null) and, for YDT >= 0, the fused
+// Requantise one wave tile (blocks from blk0, in the group that starts at
+// block gblk) and store its INT4 codes and scales (when out is not null) and, for YDT >= 0, the fused
 // dequantisation fl(code * s_out) in YDT.  ybuf: the workgroup's LDS staging
 // buffer for dequantised outputs wider than 16 bytes per lane; then every
 // wave of the workgroup must call this for the same group.
 template <int B, int E, int YDT>
-__device__ __forceinline__ void requant_tile(const float (&acc)[E], int64_t blk0, int64_t grp, int lane,
+__device__ __forceinline__ void requant_tile(const float (&acc)[E], int64_t blk0, int64_t gblk, int lane,
                                              uint8_t* __restrict__ out, float* __restrict__ sout,
                                              void* __restrict__ y, u32x4* ybuf) {
-  constexpr int L = B / E, NW = E / 8, GB = kThreads / 64 * (64 / L);
+  constexpr int L = B / E, NW = E / 8;
   constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();  // dequantised bytes per lane
   float a = fabsf(acc[0]);
 #pragma unroll
@@ -616,7 +651,7 @@ __device__ __forceinline__ void requant_tile(const float (&acc)[E], int64_t blk0
     if constexpr (YB > 16) {  // every wave of the workgroup is here, at the same group
       store_elems<0, YDT, E>(reinterpret_cast<char*>(ybuf) + threadIdx.x * YB, 0, v);
       __syncthreads();
-      u32x4* dst = reinterpret_cast<u32x4*>(static_cast<char*>(y) + grp * GB * B * elem_size<YDT>());
+      u32x4* dst = reinterpret_cast<u32x4*>(static_cast<char*>(y) + gblk * B * elem_size<YDT>());
 #pragma unroll
       for (int c = 0; c < YB / 16; ++c)
         st<ZQ_NT_DEQ4>(dst + c * kThreads + threadIdx.x, ybuf[c * kThreads + threadIdx.x]);
@@ -627,226 +662,51 @@ __device__ __forceinline__ void requant_tile(const float (&acc)[E], int64_t blk0
   }
 }
 
-template <int U, int NW>
-struct SliceBatch {
-  uint32_t w[U][NW];
-  float s[U];
-};
-
-// GATHER: the slices are not back to back; `in` and `sin` point to device
-// tables of P slice pointers (bytes, scales) instead, e.g. the peers' send
-// buffers mapped into this GPU's address space.
-template <int B, int E, int U, int TR, bool PIPE, int YDT, bool GATHER = false>
-__global__ void __launch_bounds__(kThreads) k_reduce(const uint8_t* __restrict__ in, const float* __restrict__ sin,
-                                                     int P, int64_t slice_bytes, int64_t slice_scales,
-                                                     int64_t nfull, uint8_t* __restrict__ out,
-                                                     float* __restrict__ sout, void* __restrict__ y) {
-  constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW;
-  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4) && TR >= 1, "lane layout");
-  constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();  // dequantised bytes per lane
-  constexpr bool YSTAGE = YB > 16;
-  __shared__ u32x4 ybuf[YSTAGE ? kThreads * YB / 16 : 1];
+// One block of len <= B elements by one wave (the short last block of a level,
+// and every block of a level smaller than one group): plain arithmetic, the
+// definition as written, sum from +0, one multiply and one add per slice.  A
+// lane owns byte j = lane + 64 i of the block (elements 2j, 2j + 1).  The
+// loads of 8 slices are in flight together (past the end: byte nbytes - 1
+// and slice P - 1 again, unused).
+template <int B, typename Src>
+__device__ __forceinline__ void reduce_block(const Src& src, int P, int64_t blk, int len, uint8_t* __restrict__ out,
+                                             float* __restrict__ sout, void* __restrict__ y, int ydt) {
+  constexpr int I = B > 128 ? B / 128 : 1, U = 8;
   const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane_byte = lane * (E / 2);
-
-  const int64_t g0 = (int64_t)blockIdx.x * TR;  // first group of this workgroup
-  const int64_t groups = nfull / GB;
-  const int ng = (int)(groups - g0 >= TR ? TR : groups - g0);  // >= 1 by the launch size
-  const int nb = (P + U - 1) / U;
-  auto tile_blk0 = [&](int64_t grp) { return (grp * WPG + wv) * BPW; };
-
-  // slices [b*U, b*U + U) of this wave's tile of group grp
-  auto issue = [&](SliceBatch<U, NW>& X, int64_t grp, int b) {
-    const int64_t blk0 = tile_blk0(grp);
+  const int nbytes = (len + 1) >> 1;
+  const int64_t base = blk * B;
+  float acc[2 * I];
+#pragma unroll
+  for (int k = 0; k < 2 * I; ++k) acc[k] = 0.0f;
+#pragma unroll 1
+  for (int p0 = 0; p0 < P; p0 += U) {
+    uint32_t w[U][I];
+    float s[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = b * U + u;
-      if (p < P) {
-        const uint8_t* tb;
-        const float* sb;
-        if constexpr (GATHER) {
-          tb = reinterpret_cast<const uint8_t* const*>(in)[p] + blk0 * (B / 2);
-          sb = reinterpret_cast<const float* const*>(sin)[p] + blk0;
-        } else {
-          tb = in + blk0 * (B / 2) + (int64_t)p * slice_bytes;
-          sb = sin + blk0 + (int64_t)p * slice_scales;
+      const int p = p0 + u < P ? p0 + u : P - 1;
+      const uint8_t* b = src.bytes(p) + (base >> 1);
+      s[u] = src.scales(p)[blk];
+#pragma unroll
+      for (int i = 0; i < I; ++i) {
+        const int j = lane + 64 * i;
+        w[u][i] = b[j < nbytes ? j : nbytes - 1];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (p0 + u < P) {
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+          acc[2 * i] = acc[2 * i] + nib_to_f32(w[u][i], 0) * s[u];
+          acc[2 * i + 1] = acc[2 * i + 1] + nib_to_f32(w[u][i], 1) * s[u];
         }
-        load_words<ZQ_NT_REDUCE, NW>(tb + lane_byte, X.w[u]);
-        X.s[u] = ld<ZQ_NT_REDUCE>(sb + lane / L);
-      }
-    }
-  };
-
-  float acc[E];
-  auto sum_batch = [&](const SliceBatch<U, NW>& X, int b) {
-    if (b == 0) add_slice<E, NW, true>(acc, X.w[0], X.s[0]);
-    else add_slice<E, NW, false>(acc, X.w[0], X.s[0]);
-#pragma unroll
-    for (int u = 1; u < U; ++u)
-      if (b * U + u < P) add_slice<E, NW, false>(acc, X.w[u], X.s[u]);
-  };
-  // requantise this wave's tile of group grp and store it
-  auto finish = [&](int64_t grp) { requant_tile<B, E, YDT>(acc, tile_blk0(grp), grp, lane, out, sout, y, ybuf); };
-
-  SliceBatch<U, NW> A;
-  if constexpr (!PIPE) {
-#pragma unroll 1
-    for (int t = 0; t < ng; ++t) {
-#pragma unroll 1
-      for (int b = 0; b < nb; ++b) {
-        issue(A, g0 + t, b);
-        sum_batch(A, b);
-      }
-      finish(g0 + t);
-    }
-  } else {
-    // jobs (group g0 + t, batch b) in order, two buffers alternating
-    SliceBatch<U, NW> Bf;
-    const int njobs = ng * nb;
-    int it = 0, ib = 0, ct = 0, cb = 0;  // next job to issue / to consume
-    auto next = [&](int& t, int& b) {
-      if (++b == nb) {
-        b = 0;
-        ++t;
-      }
-    };
-    issue(A, g0 + it, ib);
-    next(it, ib);
-#pragma unroll 1
-    for (int j = 0; j < njobs; j += 2) {
-      if (j + 1 < njobs) {
-        issue(Bf, g0 + it, ib);
-        next(it, ib);
-      }
-      sum_batch(A, cb);
-      if (cb == nb - 1) finish(g0 + ct);
-      next(ct, cb);
-      if (j + 2 < njobs) {
-        issue(A, g0 + it, ib);
-        next(it, ib);
-      }
-      if (j + 1 < njobs) {
-        sum_batch(Bf, cb);
-        if (cb == nb - 1) finish(g0 + ct);
-        next(ct, cb);
-      }
-    }
-  }
-}
-
-// Vector path with the slice count fixed at compile time (PC = 2, 4 or 8;
-// E = 32 on large levels, E = 8 on small ones).  Same lane layout,
-// arithmetic and order as k_reduce, but every load is
-// unconditional, so the compiler waits for each slice's data on its own
-// (s_waitcnt vmcnt(n) counting the loads issued after it) instead of for
-// every load in flight, and the sum of slice 0 starts while the others are
-// still arriving.  A workgroup takes TRC consecutive groups; with TRC > 1 the
-// loads of a wave's next tile are issued before its current tile is summed,
-// so they arrive while it computes (two register buffers).  The last
-// workgroup clamps its group index to the last group and recomputes it,
-// rewriting identical values, instead of branching around loads.
-#ifndef ZQ_FIXED_WAVES
-#define ZQ_FIXED_WAVES 0
-#endif
-#if ZQ_FIXED_WAVES
-#define ZQ_FIXED_ATTR __attribute__((amdgpu_waves_per_eu(ZQ_FIXED_WAVES)))
-#else
-#define ZQ_FIXED_ATTR
-#endif
-template <int B, int E, int PC, int TRC, int YDT, bool GATHER>
-__global__ void __launch_bounds__(kThreads) ZQ_FIXED_ATTR k_reduce_p(const uint8_t* __restrict__ in, const float* __restrict__ sin,
-                                                       int, int64_t slice_bytes, int64_t slice_scales, int64_t nfull,
-                                                       uint8_t* __restrict__ out, float* __restrict__ sout,
-                                                       void* __restrict__ y) {
-  constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW, NBUF = TRC > 1 ? 2 : 1;
-  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4) && PC >= 1 && TRC >= 1, "lane layout");
-  constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();
-  __shared__ u32x4 ybuf[YB > 16 ? kThreads * YB / 16 : 1];
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane_byte = lane * (E / 2);
-  const int64_t last = nfull / GB - 1;                  // last group
-  const int64_t g0 = (int64_t)blockIdx.x * TRC;
-  auto group_of = [&](int t) { return g0 + t < last ? g0 + t : last; };
-  auto tile_blk0 = [&](int64_t grp) { return (grp * WPG + wv) * BPW; };
-
-  uint32_t w[NBUF][PC][NW];
-  float sc[NBUF][PC];
-  auto issue = [&](int buf, int64_t grp) {
-    const int64_t blk0 = tile_blk0(grp);
-#pragma unroll
-    for (int p = 0; p < PC; ++p) {
-      const uint8_t* tb;
-      const float* sb;
-      if constexpr (GATHER) {
-        tb = reinterpret_cast<const uint8_t* const*>(in)[p] + blk0 * (B / 2);
-        sb = reinterpret_cast<const float* const*>(sin)[p] + blk0;
-      } else {
-        tb = in + blk0 * (B / 2) + (int64_t)p * slice_bytes;
-        sb = sin + blk0 + (int64_t)p * slice_scales;
-      }
-      load_words<ZQ_NT_REDUCE, NW>(tb + lane_byte, w[buf][p]);
-      sc[buf][p] = ld<ZQ_NT_REDUCE>(sb + lane / L);
-    }
-  };
-
-  prio_issue<ZQ_PRIO_REDUCE>();
-  issue(0, group_of(0));
-  prio_compute<ZQ_PRIO_REDUCE>();
-#pragma unroll
-  for (int t = 0; t < TRC; ++t) {
-    if (t + 1 < TRC) {
-      prio_issue<ZQ_PRIO_REDUCE>();
-      issue((t + 1) % NBUF, group_of(t + 1));
-      prio_compute<ZQ_PRIO_REDUCE>();
-    }
-    const int b = t % NBUF;
-    float acc[E];
-    add_slice<E, NW, true>(acc, w[b][0], sc[b][0]);
-#pragma unroll
-    for (int p = 1; p < PC; ++p) add_slice<E, NW, false>(acc, w[b][p], sc[b][p]);
-    const int64_t grp = group_of(t);
-    requant_tile<B, E, YDT>(acc, tile_blk0(grp), grp, lane, out, sout, y, ybuf);
-  }
-}
-
-// Generic path: any m, any slice alignment; one wave per block, blocks
-// [blk_begin, blk_begin + gridDim.x).  A lane owns byte j = lane + 64 i of the
-// block (elements 2j, 2j+1), i < B/128 rounded up.  Plain arithmetic, the
-// definition as written: sum from +0, one multiply and one add per slice.
-// GATHER as for k_reduce.
-template <bool GATHER>
-__global__ void __launch_bounds__(64) k_reduce_generic(const uint8_t* __restrict__ in, const float* __restrict__ sin,
-                                                       int P, int64_t slice_bytes, int64_t slice_scales, int64_t m,
-                                                       int B, int64_t blk_begin, uint8_t* __restrict__ out,
-                                                       float* __restrict__ sout, void* __restrict__ y, int ydt) {
-  constexpr int MAXI = 1024 / 128;
-  const int lane = threadIdx.x;
-  const int64_t blk = blk_begin + blockIdx.x;
-  const int64_t base = blk * B;
-  const int len = (int)((m - base) < B ? (m - base) : B);
-  const int nbytes = (len + 1) >> 1;
-  float acc[2 * MAXI];
-#pragma unroll
-  for (int k = 0; k < 2 * MAXI; ++k) acc[k] = 0.0f;
-  for (int p = 0; p < P; ++p) {
-    const float s = GATHER ? reinterpret_cast<const float* const*>(sin)[p][blk] : sin[(int64_t)p * slice_scales + blk];
-    const uint8_t* src =
-        (GATHER ? reinterpret_cast<const uint8_t* const*>(in)[p] : in + (int64_t)p * slice_bytes) + (base >> 1);
-#pragma unroll
-    for (int i = 0; i < MAXI; ++i) {
-      const int j = lane + 64 * i;
-      if (j < nbytes) {
-        const uint32_t byte = src[j];
-        acc[2 * i] = acc[2 * i] + nib_to_f32(byte, 0) * s;
-        acc[2 * i + 1] = acc[2 * i + 1] + nib_to_f32(byte, 1) * s;
       }
     }
   }
   float a = 0.0f;
 #pragma unroll
-  for (int i = 0; i < MAXI; ++i) {
+  for (int i = 0; i < I; ++i) {
     const int j = lane + 64 * i;
     if (j < nbytes) {
       a = fmaxf(a, fabsf(acc[2 * i]));
@@ -860,13 +720,13 @@ __global__ void __launch_bounds__(64) k_reduce_generic(const uint8_t* __restrict
     r = 7.0f / amax;
   }
 #pragma unroll
-  for (int i = 0; i < MAXI; ++i) {
+  for (int i = 0; i < I; ++i) {
     const int j = lane + 64 * i;
     if (j < nbytes) {
       const uint32_t lo = code_bits(acc[2 * i], r);
       const uint32_t hi = (2 * j + 1 < len) ? code_bits(acc[2 * i + 1], r) : 0u;
       if (out != nullptr) out[(base >> 1) + j] = (uint8_t)((lo & 0xfu) | ((hi & 0xfu) << 4));
-      if (y != nullptr) {
+      if (ydt >= 0) {
         const float v0 = (u2f(lo) - kRoundMagic) * so, v1 = (u2f(hi) - kRoundMagic) * so;
         const int64_t i0 = base + 2 * j;
         if (ydt == ZQ_F32) store1<ZQ_F32>(y, i0, v0);
@@ -881,6 +741,157 @@ __global__ void __launch_bounds__(64) k_reduce_generic(const uint8_t* __restrict
     }
   }
   if (lane == 0 && out != nullptr) sout[blk] = so;
+}
+
+// Levels smaller than one group: one wave per block, the last one short when
+// B does not divide m.
+template <int B, typename Src>
+__global__ void __launch_bounds__(64) k_reduce_blocks(Src src, int P, int64_t m, uint8_t* __restrict__ out,
+                                                      float* __restrict__ sout, void* __restrict__ y, int ydt) {
+  const int64_t blk = blockIdx.x, rest = m - blk * B;
+  reduce_block<B>(src, P, blk, (int)(rest < B ? rest : B), out, sout, y, ydt);
+}
+
+template <int U, int NW>
+struct SliceBatch {
+  uint32_t w[U][NW];
+  float s[U];
+};
+
+// Any slice count.  Slices are loaded U at a time (a batch); with PIPE into two
+// register buffers, the next batch in flight while one is summed.  Every load is
+// unconditional (the last batch loads slice P - 1 again in place of the
+// slices it lacks, and leaves those out of the sum), so the compiler waits for
+// exactly the loads that it needs; branches around loads make it wait for all
+// (P = 3, m = 20,000,000, B = 128: 13.9 -> 11.7 us; P = 5, m = 30,000,000,
+// B = 512: 26.0 -> 21.3 us).  Batches of 3 where 3 divides P, else 4.  Small
+// levels (E = 8) have up to 8 waves per SIMD to overlap instead: one buffer of
+// 8 slices (P = 16, m = 3,000,000, B = 64: 15.7 us with 16 slices behind
+// branches, 10.3 with 16, 9.2 with 8; two buffers of 8: 9.5).
+template <int B, int E, int U, bool PIPE, int YDT, typename Src>
+__global__ void __launch_bounds__(kThreads) k_reduce(Src src, int P, int64_t nfull, int tail, unsigned tail_wg,
+                                                     uint8_t* __restrict__ out, float* __restrict__ sout,
+                                                     void* __restrict__ y) {
+  constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW;
+  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4), "lane layout");
+  constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();  // dequantised bytes per lane
+  __shared__ u32x4 ybuf[YB > 16 ? kThreads * YB / 16 : 1];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (blockIdx.x == tail_wg) {
+    if (wv == 0) reduce_block<B>(src, P, nfull, tail, out, sout, y, YDT);
+    return;
+  }
+  const unsigned lane_byte = lane * (E / 2), lane_scale = lane / L;
+  const int64_t last = nfull - GB, first = (int64_t)blockIdx.x * GB;
+  const int64_t gblk = uniform(first < last ? first : last), blk0 = gblk + wv * BPW;
+  const int nb = (P + U - 1) / U;
+
+  // slices [b*U, b*U + U) of this wave's tile; CLAMP: slice P - 1 in the place
+  // of those past it
+  auto issue = [&](SliceBatch<U, NW>& X, int b, auto clamp) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = !decltype(clamp)::value || b * U + u < P ? b * U + u : P - 1;
+      load_slice(src.bytes(p) + blk0 * (B / 2), lane_byte, src.scales(p) + blk0, lane_scale, X.w[u], X.s[u]);
+    }
+  };
+  constexpr std::true_type kClamp{};
+  constexpr std::false_type kWhole{};
+  float acc[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) acc[k] = 0.0f;
+  auto sum = [&](const SliceBatch<U, NW>& X) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) add_slice<E, NW, false, true>(acc, X.w[u], X.s[u]);
+  };
+  auto sum_last = [&](const SliceBatch<U, NW>& X) {
+    add_slice<E, NW, false, true>(acc, X.w[0], X.s[0]);
+#pragma unroll
+    for (int u = 1; u < U; ++u)
+      if ((nb - 1) * U + u < P) add_slice<E, NW, false, true>(acc, X.w[u], X.s[u]);
+  };
+
+  SliceBatch<U, NW> X0;
+  if constexpr (PIPE) {
+    SliceBatch<U, NW> X1;
+    issue(X0, 0, kClamp);
+    int b = 0;
+#pragma unroll 1
+    for (; b + 2 < nb; b += 2) {
+      issue(X1, b + 1, kWhole);
+      sum(X0);
+      issue(X0, b + 2, kClamp);
+      sum(X1);
+    }
+    if (b + 1 < nb) {
+      issue(X1, b + 1, kClamp);
+      sum(X0);
+      sum_last(X1);
+    } else {
+      sum_last(X0);
+    }
+  } else {
+#pragma unroll 1
+    for (int b = 0; b < nb - 1; ++b) {
+      issue(X0, b, kWhole);
+      sum(X0);
+    }
+    issue(X0, nb - 1, kClamp);
+    sum_last(X0);
+  }
+  requant_tile<B, E, YDT>(acc, blk0, gblk, lane, out, sout, y, ybuf);
+}
+
+// The slice count fixed at compile time (PC = 2, 4 or 8; E = 32 on large
+// levels, E = 8 on small ones).  Same lane layout, arithmetic and order as
+// k_reduce, with all of a tile's slices loaded at once: the compiler waits for
+// each slice's data on its own (s_waitcnt vmcnt(n) counting the loads issued
+// after it), and the sum of slice 0 starts while the others are still
+// arriving.  A workgroup takes TRC consecutive groups; with TRC > 1 the loads
+// of a wave's next tile are issued before its current tile is summed, so they
+// arrive while it computes (two register buffers).  The last workgroup clamps
+// its group index to the last group and recomputes it.
+template <int B, int E, int PC, int TRC, int YDT, typename Src>
+__global__ void __launch_bounds__(kThreads) k_reduce_p(Src src, int, int64_t nfull, int tail, unsigned tail_wg,
+                                                       uint8_t* __restrict__ out, float* __restrict__ sout,
+                                                       void* __restrict__ y) {
+  constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW, NBUF = TRC > 1 ? 2 : 1;
+  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4) && PC >= 1 && TRC >= 1, "lane layout");
+  constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();
+  __shared__ u32x4 ybuf[YB > 16 ? kThreads * YB / 16 : 1];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (blockIdx.x == tail_wg) {
+    if (wv == 0) reduce_block<B>(src, PC, nfull, tail, out, sout, y, YDT);
+    return;
+  }
+  const unsigned lane_byte = lane * (E / 2), lane_scale = lane / L;
+  const int64_t last = nfull - GB, first = (int64_t)blockIdx.x * (TRC * GB);
+  auto group_blk = [&](int t) { return uniform(first + t * GB < last ? first + t * GB : last); };
+
+  uint32_t w[NBUF][PC][NW];
+  float sc[NBUF][PC];
+  auto issue = [&](int buf, int64_t gblk) {
+    const int64_t blk0 = gblk + wv * BPW;
+#pragma unroll
+    for (int p = 0; p < PC; ++p) {
+      load_slice(src.bytes(p) + blk0 * (B / 2), lane_byte, src.scales(p) + blk0, lane_scale, w[buf][p], sc[buf][p]);
+    }
+  };
+
+  issue(0, group_blk(0));
+#pragma unroll
+  for (int t = 0; t < TRC; ++t) {
+    if (t + 1 < TRC) issue((t + 1) % NBUF, group_blk(t + 1));
+    const int b = t % NBUF;
+    float acc[E];
+    add_slice<E, NW, true>(acc, w[b][0], sc[b][0]);
+#pragma unroll
+    for (int p = 1; p < PC; ++p) add_slice<E, NW, false>(acc, w[b][p], sc[b][p]);
+    const int64_t gblk = group_blk(t);
+    requant_tile<B, E, YDT>(acc, gblk + wv * BPW, gblk, lane, out, sout, y, ybuf);
+  }
 }
 
 // ------------------------------------------------------------------ address tables
@@ -929,136 +940,66 @@ DequantKernel dequant_kernel(int dt, int qbits) {
   return &k_dequant<ZQ_BF16, 4>;
 }
 
-template <int YDT>
-static ReduceKernel reduce_kernel_for(int lgB, ReduceShape shape) {
-  // large: E = 32, U = 4; two slices: E = 32, U = 2, two tiles per wave with the
-  // next tile's loads issued before this tile's requantisation; small: E = 8,
-  // U = 16.  A block may span at most one wave, so B = 1024 always takes large.
-  constexpr int EL = kReduceElems, UL = ZQ_REDUCE_U, ES = kReduceElemsSmall, US = ZQ_REDUCE_U_SMALL;
-  constexpr int TL = reduce_tiles(ReduceShape::kLarge), T2 = reduce_tiles(ReduceShape::kTwoSlices),
-                TS = reduce_tiles(ReduceShape::kSmall);
-  constexpr bool PL = ZQ_REDUCE_PIPE, P2 = ZQ_REDUCE_PIPE2, PS = ZQ_REDUCE_PIPE_SMALL;
-#define ZQ_REDUCE_CASE(LG, BB)                                                                       \
-  case LG:                                                                                           \
-    if (shape == ReduceShape::kSmall) return &k_reduce<BB, ES, US, TS, PS, YDT>;                     \
-    if (shape == ReduceShape::kTwoSlices) return &k_reduce<BB, EL, 2, T2, P2, YDT>;                  \
-    return &k_reduce<BB, EL, UL, TL, PL, YDT>;
+// The reduce kernel of a level: P = 2, 4 and 8 fixed at compile time for B = 64,
+// 128 and 256 (with two slices on large levels a workgroup takes four groups),
+// any other count by batches of U slices.
+template <int B, int YDT, typename Src>
+static ReduceKernel<Src> reduce_kernel_for(int P, bool small) {
+  constexpr int EL = kReduceElems, ES = kReduceElemsSmall;
+  if constexpr (B >= 64 && B <= 256) {
+    if (P == 2) return small ? &k_reduce_p<B, ES, 2, 1, YDT, Src> : &k_reduce_p<B, EL, 2, fixed_groups(2), YDT, Src>;
+    if (P == 4) return small ? &k_reduce_p<B, ES, 4, 1, YDT, Src> : &k_reduce_p<B, EL, 4, fixed_groups(4), YDT, Src>;
+    if (P == 8) return small ? &k_reduce_p<B, ES, 8, 1, YDT, Src> : &k_reduce_p<B, EL, 8, fixed_groups(8), YDT, Src>;
+  }
+  if constexpr (B <= 512) {
+    if (small) return &k_reduce<B, ES, 8, false, YDT, Src>;
+  }
+  if (P % 3 == 0 && P % 4 != 0) return &k_reduce<B, EL, 3, true, YDT, Src>;
+  return &k_reduce<B, EL, 4, true, YDT, Src>;
+}
+
+template <int YDT, typename Src>
+static ReduceKernel<Src> reduce_kernel_b(int lgB, int P, bool small) {
   switch (lgB) {
-    ZQ_REDUCE_CASE(5, 32)
-    ZQ_REDUCE_CASE(6, 64)
-    ZQ_REDUCE_CASE(7, 128)
-    ZQ_REDUCE_CASE(8, 256)
-    ZQ_REDUCE_CASE(9, 512)
-    default: return &k_reduce<1024, EL, UL, TL, PL, YDT>;
+    case 5: return reduce_kernel_for<32, YDT, Src>(P, small);
+    case 6: return reduce_kernel_for<64, YDT, Src>(P, small);
+    case 7: return reduce_kernel_for<128, YDT, Src>(P, small);
+    case 8: return reduce_kernel_for<256, YDT, Src>(P, small);
+    case 9: return reduce_kernel_for<512, YDT, Src>(P, small);
+    default: return reduce_kernel_for<1024, YDT, Src>(P, small);
   }
-#undef ZQ_REDUCE_CASE
 }
 
-ReduceKernel reduce_kernel(int lgB, ReduceShape shape, int ydt) {
+template <>
+ReduceKernel<SlicesInRow> reduce_kernel(int lgB, int P, bool small, int ydt) {
   switch (ydt) {
-    case ZQ_F32: return reduce_kernel_for<ZQ_F32>(lgB, shape);
-    case ZQ_F16: return reduce_kernel_for<ZQ_F16>(lgB, shape);
-    case ZQ_BF16: return reduce_kernel_for<ZQ_BF16>(lgB, shape);
-    default: return reduce_kernel_for<-1>(lgB, shape);
+    case ZQ_F32: return reduce_kernel_b<ZQ_F32, SlicesInRow>(lgB, P, small);
+    case ZQ_F16: return reduce_kernel_b<ZQ_F16, SlicesInRow>(lgB, P, small);
+    case ZQ_BF16: return reduce_kernel_b<ZQ_BF16, SlicesInRow>(lgB, P, small);
+    default: return reduce_kernel_b<-1, SlicesInRow>(lgB, P, small);
   }
 }
 
-ReduceKernel reduce_gather_kernel(int lgB, ReduceShape shape) {
-  constexpr int EL = kReduceElems, UL = ZQ_REDUCE_U, ES = kReduceElemsSmall, US = ZQ_REDUCE_U_SMALL;
-  constexpr int TL = reduce_tiles(ReduceShape::kLarge), T2 = reduce_tiles(ReduceShape::kTwoSlices),
-                TS = reduce_tiles(ReduceShape::kSmall);
-  constexpr bool PL = ZQ_REDUCE_PIPE, P2 = ZQ_REDUCE_PIPE2, PS = ZQ_REDUCE_PIPE_SMALL;
-#define ZQ_GATHER_CASE(LG, BB)                                                                        \
-  case LG:                                                                                            \
-    if (shape == ReduceShape::kSmall) return &k_reduce<BB, ES, US, TS, PS, -1, true>;                 \
-    if (shape == ReduceShape::kTwoSlices) return &k_reduce<BB, EL, 2, T2, P2, -1, true>;              \
-    return &k_reduce<BB, EL, UL, TL, PL, -1, true>;
+template <>
+ReduceKernel<SlicesInTable> reduce_kernel(int lgB, int P, bool small, int) {
+  return reduce_kernel_b<-1, SlicesInTable>(lgB, P, small);
+}
+
+template <typename Src>
+static ReduceBlocksKernel<Src> reduce_blocks_b(int lgB) {
   switch (lgB) {
-    ZQ_GATHER_CASE(5, 32)
-    ZQ_GATHER_CASE(6, 64)
-    ZQ_GATHER_CASE(7, 128)
-    ZQ_GATHER_CASE(8, 256)
-    ZQ_GATHER_CASE(9, 512)
-    default: return &k_reduce<1024, EL, UL, TL, PL, -1, true>;
-  }
-#undef ZQ_GATHER_CASE
-}
-
-#ifndef ZQ_FIXED_TR2
-#define ZQ_FIXED_TR2 4
-#endif
-#ifndef ZQ_FIXED_TR4
-#define ZQ_FIXED_TR4 1
-#endif
-#ifndef ZQ_FIXED_TR8
-#define ZQ_FIXED_TR8 1
-#endif
-constexpr int fixed_tiles(int P) { return P == 2 ? ZQ_FIXED_TR2 : P == 4 ? ZQ_FIXED_TR4 : ZQ_FIXED_TR8; }
-int reduce_fixed_tiles(int P) { return fixed_tiles(P); }
-
-#ifndef ZQ_FIXED_E
-#define ZQ_FIXED_E 32
-#endif
-#ifndef ZQ_FIXED_SMALL
-#define ZQ_FIXED_SMALL 1
-#endif
-int reduce_fixed_elems() { return ZQ_FIXED_E; }
-
-template <int B, int YDT, bool GATHER>
-static ReduceKernel reduce_fixed_for_b(int P) {
-  constexpr int E = ZQ_FIXED_E;
-  if (P == 2) return &k_reduce_p<B, E, 2, fixed_tiles(2), YDT, GATHER>;
-  if (P == 4) return &k_reduce_p<B, E, 4, fixed_tiles(4), YDT, GATHER>;
-  return &k_reduce_p<B, E, 8, fixed_tiles(8), YDT, GATHER>;
-}
-
-template <int YDT, bool GATHER>
-static ReduceKernel reduce_fixed_for(int lgB, int P) {
-  if (lgB == 6) return reduce_fixed_for_b<64, YDT, GATHER>(P);
-  if (lgB == 7) return reduce_fixed_for_b<128, YDT, GATHER>(P);
-  return reduce_fixed_for_b<256, YDT, GATHER>(P);
-}
-
-ReduceKernel reduce_fixed_kernel(int lgB, int P, int ydt, bool gather) {
-  if (lgB < 6 || lgB > 8 || (P != 2 && P != 4 && P != 8) || (gather && ydt >= 0)) return nullptr;
-  if (gather) return reduce_fixed_for<-1, true>(lgB, P);
-  switch (ydt) {
-    case ZQ_F32: return reduce_fixed_for<ZQ_F32, false>(lgB, P);
-    case ZQ_F16: return reduce_fixed_for<ZQ_F16, false>(lgB, P);
-    case ZQ_BF16: return reduce_fixed_for<ZQ_BF16, false>(lgB, P);
-    default: return reduce_fixed_for<-1, false>(lgB, P);
+    case 5: return &k_reduce_blocks<32, Src>;
+    case 6: return &k_reduce_blocks<64, Src>;
+    case 7: return &k_reduce_blocks<128, Src>;
+    case 8: return &k_reduce_blocks<256, Src>;
+    case 9: return &k_reduce_blocks<512, Src>;
+    default: return &k_reduce_blocks<1024, Src>;
   }
 }
 
-// Small levels (E = 8, the small-level group size): P = 2, 4, 8 fixed at
-// compile time, one group per workgroup.
-template <int B, int YDT, bool GATHER>
-static ReduceKernel reduce_fixed_small_for_b(int P) {
-  if (P == 2) return &k_reduce_p<B, 8, 2, 1, YDT, GATHER>;
-  if (P == 4) return &k_reduce_p<B, 8, 4, 1, YDT, GATHER>;
-  return &k_reduce_p<B, 8, 8, 1, YDT, GATHER>;
-}
-
-template <int YDT, bool GATHER>
-static ReduceKernel reduce_fixed_small_for(int lgB, int P) {
-  if (lgB == 6) return reduce_fixed_small_for_b<64, YDT, GATHER>(P);
-  if (lgB == 7) return reduce_fixed_small_for_b<128, YDT, GATHER>(P);
-  return reduce_fixed_small_for_b<256, YDT, GATHER>(P);
-}
-
-ReduceKernel reduce_fixed_small_kernel(int lgB, int P, int ydt, bool gather) {
-  if (!ZQ_FIXED_SMALL || lgB < 6 || lgB > 8 || (P != 2 && P != 4 && P != 8) || (gather && ydt >= 0)) return nullptr;
-  if (gather) return reduce_fixed_small_for<-1, true>(lgB, P);
-  switch (ydt) {
-    case ZQ_F32: return reduce_fixed_small_for<ZQ_F32, false>(lgB, P);
-    case ZQ_F16: return reduce_fixed_small_for<ZQ_F16, false>(lgB, P);
-    case ZQ_BF16: return reduce_fixed_small_for<ZQ_BF16, false>(lgB, P);
-    default: return reduce_fixed_small_for<-1, false>(lgB, P);
-  }
-}
-
-ReduceGenericKernel reduce_generic_kernel(bool gather) {
-  return gather ? &k_reduce_generic<true> : &k_reduce_generic<false>;
-}
+template <>
+ReduceBlocksKernel<SlicesInRow> reduce_blocks_kernel(int lgB) { return reduce_blocks_b<SlicesInRow>(lgB); }
+template <>
+ReduceBlocksKernel<SlicesInTable> reduce_blocks_kernel(int lgB) { return reduce_blocks_b<SlicesInTable>(lgB); }
 
 }  // namespace zq
