@@ -150,7 +150,8 @@ int qgz_reduce_level_gather(const uint8_t* const* packed_slices, const float* co
 /* Allocation-free form of qgz_reduce_level_gather, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  The P slice addresses come in HOST
- * arrays; the library writes them into a static device table of its own (one
+ * arrays.  Up to 64 slices they travel as arguments of the one kernel launched;
+ * for more the library writes them into a static device table of its own (one
  * per GPU, 2048 addresses = 16 KiB, held until the process ends) with small
  * kernels on `stream` whose values travel as kernel arguments, then runs the
  * gathered reduce over them.  Nothing is allocated and nothing synchronises.
@@ -162,9 +163,10 @@ int qgz_reduce_level_gather(const uint8_t* const* packed_slices, const float* co
  * host, every slice is checked: non-null (ZQ_E_NULL), 16-byte aligned when
  * m % 32 == 0 and scale slices 4-byte aligned (ZQ_E_ALIGN), no overlap with
  * an output (ZQ_E_ALIAS).  The table belongs to the current device, and
- * `stream` must belong to it too.  Every call on one GPU uses the same table:
- * calls that can overlap on one GPU (different streams, or different host
- * threads without ordering) race on it; calls on one stream are ordered.
+ * `stream` must belong to it too.  Every call of more than 64 slices on one GPU
+ * uses the same table: such calls that can overlap on one GPU (different
+ * streams, or different host threads without ordering) race on it; calls on one
+ * stream are ordered.
  * Results are bit-identical to qgz_reduce_level_gather (and qgz_reduce_level
  * on the slices back to back). */
 int qgz_reduce_level_gather_noalloc(const uint8_t* const* packed_slices, const float* const* scale_slices, int32_t P,

@@ -187,10 +187,22 @@ int reduce_gather_host(const uint8_t* const* packed_slices, const float* const* 
       for (const Range& i : ins)
         if (overlap(o, i)) return ZQ_E_ALIAS;
   }
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  // up to kArgSlices addresses travel with the reduce kernel's own launch (P = 8,
+  // m = 6,291,456: one launch in place of a table fill and a dependent reduce)
+  if (P <= kArgSlices) {
+    if (!aligned(packed_out, 16) || !aligned(scales_out, 4)) return ZQ_E_ALIGN;
+    if (overlap(outs[0], outs[1])) return ZQ_E_ALIAS;
+    SlicesInArgs src;
+    for (int32_t p = 0; p < kArgSlices; ++p) {
+      src.in[p] = packed_slices[p < P ? p : P - 1];
+      src.sin[p] = scale_slices[p < P ? p : P - 1];
+    }
+    return launch_reduce(src, P, m, block, log2_block(block), packed_out, scales_out, nullptr, -1, st);
+  }
   uint64_t* table = nullptr;
   int rc = scratch_on_current_device(&table);
   if (rc != ZQ_OK) return rc;
-  hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t entries = 2 * (int64_t)P;
   for (int64_t e0 = 0; e0 < entries; e0 += kTableChunk) {
     TableChunk chunk;

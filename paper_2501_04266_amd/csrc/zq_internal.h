@@ -91,6 +91,15 @@ struct SlicesInTable {
   __device__ const uint8_t* bytes(int p) const { return in[p]; }
   __device__ const float* scales(int p) const { return sin[p]; }
 };
+// The addresses themselves, as kernel arguments (1 KiB of them), for up to
+// kArgSlices slices.
+constexpr int kArgSlices = 64;
+struct SlicesInArgs {
+  const uint8_t* in[kArgSlices];
+  const float* sin[kArgSlices];
+  __device__ const uint8_t* bytes(int p) const { return in[p]; }
+  __device__ const float* scales(int p) const { return sin[p]; }
+};
 // (slices, P, full blocks, length of the short last block and the workgroup that
 // takes it (past the grid when there is none), out, scales, y)
 template <typename Src>
@@ -120,9 +129,13 @@ ReduceKernel<SlicesInRow> reduce_kernel(int lgB, int P, bool small, int ydt);
 template <>
 ReduceKernel<SlicesInTable> reduce_kernel(int lgB, int P, bool small, int ydt);
 template <>
+ReduceKernel<SlicesInArgs> reduce_kernel(int lgB, int P, bool small, int ydt);
+template <>
 ReduceBlocksKernel<SlicesInRow> reduce_blocks_kernel(int lgB);
 template <>
 ReduceBlocksKernel<SlicesInTable> reduce_blocks_kernel(int lgB);
+template <>
+ReduceBlocksKernel<SlicesInArgs> reduce_blocks_kernel(int lgB);
 // a chunk of 64-bit table entries passed by value to the table-fill kernel
 constexpr int kTableChunk = 64;
 struct TableChunk {

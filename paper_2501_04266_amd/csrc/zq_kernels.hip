@@ -985,6 +985,11 @@ ReduceKernel<SlicesInTable> reduce_kernel(int lgB, int P, bool small, int) {
   return reduce_kernel_b<-1, SlicesInTable>(lgB, P, small);
 }
 
+template <>
+ReduceKernel<SlicesInArgs> reduce_kernel(int lgB, int P, bool small, int) {
+  return reduce_kernel_b<-1, SlicesInArgs>(lgB, P, small);
+}
+
 template <typename Src>
 static ReduceBlocksKernel<Src> reduce_blocks_b(int lgB) {
   switch (lgB) {
@@ -1001,5 +1006,7 @@ template <>
 ReduceBlocksKernel<SlicesInRow> reduce_blocks_kernel(int lgB) { return reduce_blocks_b<SlicesInRow>(lgB); }
 template <>
 ReduceBlocksKernel<SlicesInTable> reduce_blocks_kernel(int lgB) { return reduce_blocks_b<SlicesInTable>(lgB); }
+template <>
+ReduceBlocksKernel<SlicesInArgs> reduce_blocks_kernel(int lgB) { return reduce_blocks_b<SlicesInArgs>(lgB); }
 
 }  // namespace zq

@@ -57,3 +57,39 @@ def test_reduce_ragged(P, m, B):
     torch.cuda.synchronize()
     assert_bits_equal(from_dev(gp), op, what + " gathered codes", B // 2)
     assert_bits_equal(from_dev(gs), os_, what + " gathered scales")
+
+
+# up to 64 slices their addresses are kernel arguments, beyond that a device
+# table; small and large levels, levels of one group and less
+@pytest.mark.parametrize("P,m,B", [(1, 4096, 128), (2, LARGE + 33, 64), (6, 2049, 128), (8, 6000, 256), (3, 1000, 1024),
+                                   (63, 2048 + 17, 32), (64, 8192, 1024), (64, 4096 + 5, 64), (65, 4096 + 5, 64)])
+def test_gather_noalloc_slice_counts(P, m, B):
+    packed, scales = _slices(P, m, B, 7 * P + m % 1000)
+    op, os_ = oracle.qgz_reduce_level(packed.reshape(-1), scales.reshape(-1), P, m, B)
+    bufs, sbufs = [to_dev(p) for p in packed], [to_dev(s) for s in scales]
+    out = (torch.full((op.size,), 0xA5, dtype=torch.uint8, device="cuda"),
+           torch.full((os_.size,), -1.0, dtype=torch.float32, device="cuda"))
+    zq.qgz_reduce_level_gather_noalloc(bufs, sbufs, m, B, *out)
+    torch.cuda.synchronize()
+    assert_bits_equal(from_dev(out[0]), op, f"P={P} m={m} B={B} codes", B // 2)
+    assert_bits_equal(from_dev(out[1]), os_, f"P={P} m={m} B={B} scales")
+
+
+def test_gather_noalloc_two_streams():
+    """Calls on different streams do not share their addresses (up to 64 slices)."""
+    P, m, B = 8, 1 << 20, 128
+    work = []
+    for k in range(2):
+        packed, scales = _slices(P, m, B, 40 + k)
+        want = oracle.qgz_reduce_level(packed.reshape(-1), scales.reshape(-1), P, m, B)
+        out = (torch.empty(m // 2, dtype=torch.uint8, device="cuda"),
+               torch.empty(m // B, dtype=torch.float32, device="cuda"))
+        work.append(([to_dev(p) for p in packed], [to_dev(s) for s in scales], out, want, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for bufs, sbufs, out, _w, st in work:
+            zq.qgz_reduce_level_gather_noalloc(bufs, sbufs, m, B, *out, stream=st)
+    torch.cuda.synchronize()
+    for k, (_b, _s, out, want, _st) in enumerate(work):
+        assert_bits_equal(from_dev(out[0]), want[0], f"stream {k} codes", B // 2)
+        assert_bits_equal(from_dev(out[1]), want[1], f"stream {k} scales")
