@@ -71,7 +71,9 @@ def int4_bytes(n):
 
 def _stream(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle alone: torch.cuda.current_stream() builds a Stream object
+        # around it, 2.8 us of a small call's 10.6
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
