@@ -15,10 +15,14 @@
 // / _f16), in an order the hardware fixes.
 //
 // Kernels:
-//   k_dqgemv     M <= 16: weight streaming on 16 x 16 x 32 MFMAs, codes loaded
-//                straight into the operand registers, x staged in LDS once
-//                per K range (see the kernel).
-//   k_dqgemm_pp  M > 16: 256 x 256 tiles (128 x 256 up to 128 rows) over 8
+//   k_dqrows     few rows (M <= 16 and K < 4 N; above, where its modelled time is
+//                the lowest: up to 32-64 rows of the layer's GEMMs, a few
+//                hundred of smaller ones): weight streaming on 16 x 16 x 32
+//                MFMAs, K taken whole by each workgroup.
+//   k_dqgemv     M <= 16 and K >= 4 N: weight streaming with K split over the
+//                grid, codes loaded straight into the operand registers, x
+//                staged in LDS once per K range.
+//   k_dqgemm_pp  the rest: 256 x 256 tiles (128 x 256 up to 128 rows) over 8
 //                waves in a ping-pong schedule, waves w and w + 4 of a SIMD
 //                half a K-step apart (one stores the next tile and reads its
 //                fragments while the other runs its MFMAs, with its loads
@@ -81,11 +85,11 @@ constexpr int64_t kDqGemmPpMaxK = int64_t(1) << 21;  // 32-bit buffer offsets in
 #define ZQ_GEMM_ATOMIC_PS 3
 #endif
 constexpr int64_t kDqGemmMaxSplits = ZQ_GEMM_PP_MAX_SPLITS;
-// Row ranges: M <= 16 the weight-streaming kernel k_dqgemv; up to
-// ZQ_GEMM_HALF_M rows the ping-pong kernel's 128 x 256 tiles; beyond, its
-// 256 x 256 tiles.  Measured over the layer's four GEMMs in sequence: the
-// streaming kernel 0.11-0.15 ms at 1-16 tokens against 0.17 for the ping-pong
-// kernel; the 128 x 256 tiles 10-14% faster than the 256 x 256 at 65-128
+// Row ranges of the split kernels: M <= 16 the weight-streaming kernel k_dqgemv;
+// up to ZQ_GEMM_HALF_M rows the ping-pong kernel's 128 x 256 tiles; beyond, its
+// 256 x 256 tiles.  Measured over the layer's four GEMMs in sequence: k_dqgemv
+// 0.11-0.15 ms at 1-16 tokens against 0.17 for the ping-pong kernel; the
+// 128 x 256 tiles 10-14% faster than the 256 x 256 at 65-128
 // rows and slower at 144-224; and both faster than a 64 x 64 few-row tile
 // kernel (since removed) from 24 rows on.
 #ifndef ZQ_GEMM_HALF_M
@@ -563,8 +567,213 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
     }
 }
 
-// Few tokens (M <= kGemvRows): a weight-streaming kernel on
-// v_mfma_f32_16x16x32.  Workgroup (g, s) takes weight rows [64 g, 64 g + 64),
+template <int XT>
+__device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
+  if constexpr (XT == ZQ_BF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                   c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c,
+                                                  0, 0, 0);
+}
+
+// Few rows of x, K taken whole: weight streaming on v_mfma_f32_16x16x32 with no
+// split over the grid.  A workgroup takes 16 NG weight rows and up to 16 MT rows
+// of x; its W waves take the 64-wide K-steps in turn, two at a time (whole
+// 128-byte lines of codes), and their partial tiles are summed through LDS at
+// the end, in wave order, and stored once: no zero fill of y, no atomic
+// additions (for few rows the fill's launch alone was 5 of 18-45 us).
+//
+// Lane l loads 16 codes of weight row l / 4 (and 16 bytes of x's row l / 4), so a
+// quarter wave covers 4 rows in whole 64-byte runs; operand lane (r, h) of the
+// MFMA, which wants row r's k = 16 h .. 16 h + 15, fetches them from lane 4 r + h
+// with ds_bpermute.  (Loaded in operand order instead, 16 rows to a quarter wave,
+// the same kernel took 1.3-1.6 times as long.)  The loop has no barriers.  Codes
+// are loaded D steps ahead.  The rows' scales are staged in LDS once: a 4-byte
+// load per row and step cost 10-20%.  With XL x is staged there too (up to 48
+// KB of it: 1-4 rows at K = 6144).
+//
+// Loads are buffer loads without predicates: rows past M or N, and steps past
+// the wave's last (kDead added to their offsets), fall outside the resource and
+// read as zero without touching memory.  The fences in the prologue keep the
+// loads in the loop's order, so that its waits count those of the steady state.
+//
+// Bound by HBM for the codes up to 4 rows or so (FC1 of the 6144-wide layer at 1
+// row, 151 MB: 34 -> 27.5 us), then by the L2's rate for codes and x together,
+// since every workgroup reads its rows of x: about 10 TB/s (16 rows 45 -> 33.5
+// us, 32 rows 58 -> 38.5, 64 rows 63 -> 51).  Hence the rows per workgroup: many
+// where N leaves enough workgroups (rows_plan).
+constexpr int kScaleLds = 8192;             // scales a workgroup can stage
+constexpr int kXLds = 49152;                // bytes of x it can
+constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
+
+template <int XT, int MT, int NG, int W, int D, bool XL>
+__global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
+                                                   const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
+                                                   int lgB, float* __restrict__ y, int ngroups, int mgroups) {
+  constexpr int RN = 16 * NG;
+  static_assert(!XL || MT == 1, "x in LDS");
+  // the row groups of x that share weight rows run on one XCD, one after the
+  // other (workgroups are dealt to the XCDs round robin)
+  const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
+  const int ng = idx / mgroups * kXcds + xcd, mg = idx % mgroups;
+  if (ng >= ngroups) return;
+  const int lane = threadIdx.x & 63, r = lane & 15, h = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t n0 = (int64_t)ng * RN, m0 = (int64_t)mg * 16 * MT;
+  const int64_t mrows = M - m0 < 16 * MT ? M - m0 : 16 * MT, nrows = N - n0 < RN ? N - n0 : RN;
+  const __amdgpu_buffer_rsrc_t xres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(x + m0 * K), (short)0, (int)(mrows * K * 2), kBufferFlags);
+  const __amdgpu_buffer_rsrc_t wres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(codes + n0 * K), (short)0, (int)(nrows * K), kBufferFlags);
+  // (n0 K is a multiple of 16 * 64 >= B)
+  const int64_t s0 = (n0 * K) >> lgB, s1 = ((n0 + nrows) * K + (1 << lgB) - 1) >> lgB;
+  const __amdgpu_buffer_rsrc_t sres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(scales + s0), (short)0, (int)((s1 - s0) * 4), kBufferFlags);
+  uint32_t xoff[MT], woff[NG];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xoff[i] = (uint32_t)(((16 * i + lane / 4) * K + 16 * (lane & 3)) * 2);
+#pragma unroll
+  for (int g = 0; g < NG; ++g) woff[g] = (uint32_t)((16 * g + lane / 4) * K + 16 * (lane & 3));
+  const int src4 = (4 * r + h) * 4;  // operand lane (r, h) takes what lane 4 r + h loaded
+  auto operand = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(src4, (int)v); };
+  // this wave's steps: pairs of them in turn, so that it uses whole 128-byte lines
+  const int ksteps = (int)(K / 64);
+  const int pairs = ksteps / 2, odd = ksteps & 1;
+  const int mypairs = (pairs - wave + W - 1) / W;
+  const int steps = 2 * mypairs + (odd && pairs % W == wave ? 1 : 0);
+  auto kof = [&](int i) { return (((i >> 1) * W + wave) * 2 + (i & 1)) * 64; };
+  // LDS: scales, then x; the partial tiles take their place at the end
+  constexpr int PART = W * MT * NG * 256, SF = kScaleLds, XF = XL ? kXLds / 4 : 0;
+  constexpr int SC = (SF / 4 + 64 * W - 1) / (64 * W), XC = (XF / 4 + 64 * W - 1) / (64 * W);
+  static_assert(SC * 64 * W * 4 == SF && XC * 64 * W * 4 == XF, "staging");
+  __shared__ float lds[SF + XF > PART ? SF + XF : PART];
+  u32x4* const xlds = reinterpret_cast<u32x4*>(lds + SF);
+  u32x4 sv[SC], xv[XL ? XC : 1];
+  uint32_t soff[NG];
+  const int granules = (int)(K / 8), xr = r < M ? r : 0;  // 16-byte pieces of a row of x
+#pragma unroll
+  for (int j = 0; j < SC; ++j)
+    sv[j] = __builtin_bit_cast(
+        u32x4, __builtin_amdgcn_raw_buffer_load_b128(sres, (int)(threadIdx.x + 64 * W * j) * 16, 0, 0));
+#pragma unroll
+  for (int g = 0; g < NG; ++g) soff[g] = (uint32_t)((16 * g + r) * K + 16 * h);
+  if constexpr (XL) {
+#pragma unroll
+    for (int j = 0; j < XC; ++j)
+      xv[j] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)(threadIdx.x + 64 * W * j) * 16, 0, 0));
+  }
+  u32x4 cw[D][NG], xw[XL ? 1 : D][MT][2];
+  auto load_w = [&](int d, int i) {
+    const int k0 = kof(i);
+    const uint32_t dead = i < steps ? 0u : kDead;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      cw[d][g] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, (int)(woff[g] + k0 + dead), 0, 0));
+  };
+  auto load_x = [&](int d, int i) {
+    if constexpr (XL) return;
+    const int k0 = kof(i);
+    const uint32_t dead = i < steps ? 0u : kDead;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        xw[d][t][s] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)(xoff[t] + 2 * k0 + dead) + 16 * s, 0, 0));
+  };
+  f32x4_t acc[MT][NG];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) acc[t][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  auto step = [&](int d, int i) {
+    u32x4 xf[MT][2];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if constexpr (XL) {
+          xf[t][s] = xlds[xr * granules + ((kof(i) / 8 + 2 * h + s) ^ (xr & 7))];
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) xf[t][s][q] = operand(xw[d][t][s][q]);
+        }
+      }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      u32x4 cf;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cf[q] = operand(cw[d][g][q]);
+      const float scf = lds[(soff[g] + kof(i)) >> lgB];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        uint32_t b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t w = cf[2 * s + (u >> 1)];
+          const int sh = (u & 1) * 16;
+          b[u] = narrow2<XT>((float)(int32_t)(int8_t)(w >> sh) * scf,
+                             (float)(int32_t)(int8_t)(w >> (sh + 8)) * scf);
+        }
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t][g] = mfma16<XT>(xf[t][s], u32x4{b[0], b[1], b[2], b[3]}, acc[t][g]);
+      }
+    }
+  };
+
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(d, d);
+    load_x(d, d);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = 0; j < SC; ++j) reinterpret_cast<u32x4*>(lds)[threadIdx.x + 64 * W * j] = sv[j];
+  if constexpr (XL) {
+#pragma unroll
+    for (int j = 0; j < XC; ++j) {
+      const int c = threadIdx.x + 64 * W * j, row = c / granules, q = c % granules;
+      if (row < M) xlds[row * granules + (q ^ (row & 7))] = xv[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int i = 0; i < steps; i += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (i + d < steps) step(d, i + d);
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(d, i + d + D);
+      load_x(d, i + d + D);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // D register e of lane l: row 4 (l / 16) + e, column l % 16
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lds[wave * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane] = acc[t][g][e];
+  __syncthreads();
+  for (int j = threadIdx.x; j < MT * NG * 256; j += 64 * W) {
+    float v = lds[j];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += lds[w * (MT * NG * 256) + j];
+    const int l = j & 63, e = (j >> 6) & 3, tg = j >> 8;
+    const int64_t m = m0 + 16 * (tg / NG) + 4 * (l >> 4) + e, n = n0 + 16 * (tg % NG) + (l & 15);
+    if (m < M && n < N) y[m * N + n] = v;
+  }
+}
+
+// Up to 16 rows of x against few weight rows with a long K: a weight-streaming
+// kernel that splits K over the grid.  Workgroup (g, s) takes weight rows [64 g, 64 g + 64),
 // 16 per wave, and the K range [s kc, min(K, (s + 1) kc)), kc <= kGemvKc.
 // Within each 256-wide chunk of that range, lane l (row l % 16 of its wave's
 // 16, lane group h = l / 16) loads the 64 codes k = 64 h .. 64 h + 63 of its
@@ -577,16 +786,6 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
 // past the range, are zero.
 constexpr int kGemvRows = 16;   // x rows (M <= kGemvRows)
 constexpr int kGemvKc = 1024;   // longest K range of a workgroup
-
-template <int XT>
-__device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
-  if constexpr (XT == ZQ_BF16)
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                   c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c,
-                                                  0, 0, 0);
-}
 
 template <int XT, bool SPLIT>
 __global__ void __launch_bounds__(256) k_dqgemv(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
@@ -700,7 +899,7 @@ DqGemmKernel dqgemm_kernel(int xt, bool split, bool pp, bool half) {
 //   ceil(tiles s / CUs) ceil(ksteps / s) step  +  [s > 1] M N s atomic
 // (step, atomic: ZQ_GEMM_PP_STEP_NS, ZQ_GEMM_ATOMIC_PS), which splits the
 // GEMMs of a few hundred rows 2-16 ways and leaves full rounds whole.
-int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double step_scale) {
+int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double step_scale, double* us) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -720,6 +919,66 @@ int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double
       best_cost = c;
     }
   }
+  *us = best_cost * 1e6 + (best > 1 ? 9.5 : 4.0);
+  return best;
+}
+
+using DqRowsKernel = void (*)(const uint16_t*, const int8_t*, const float*, int64_t, int64_t, int64_t, int, float*,
+                              int, int);
+struct RowsPlan {
+  DqRowsKernel kernel;  // null: not for these sizes
+  unsigned threads;
+  int64_t ngroups, mgroups, grid;
+  double us;  // modelled time
+};
+
+// Whether and how k_dqrows runs M rows.  Its time is modelled as a launch and the
+// busiest CU's bytes of codes and x at that CU's share of what the L2s deliver:
+//   4 us + ceil(workgroups / 256) (16 NG + 32 MT) K / (45 bytes per ns)
+// (measured within 15%: 64 rows, FC1 of the 6144-wide layer 52 against 51 us, QKV
+// 52 against 51, attention output 26 against 23, FC1 of the 2048-wide layer 11.3
+// against 11.4; the workgroup of 64 weight rows keeps fewer loads in flight, 34
+// bytes per ns).  The tiled kernels' model (large_splits) gives 62, 49, 30 and 22
+// there, 63, 50, 28 and 20 measured.
+RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
+  RowsPlan best{};
+  auto take = [&](DqRowsKernel bf16, DqRowsKernel f16, int mt, int ng, int w, int few, double rate) {
+    if (((16 * ng * K) >> lgB) + 1 > kScaleLds) return;  // its rows' scales have to fit LDS
+    const int64_t ngroups = (N + 16 * ng - 1) / (16 * ng), mgroups = (M + 16 * mt - 1) / (16 * mt);
+    const int64_t wgs = ngroups * mgroups;
+    if (few >= 0 && (wgs <= 256) != (few == 1)) return;
+    const double us = 4.0 + (double)((wgs + 255) / 256) * (double)((16 * ng + 32 * mt) * K) / rate * 1e-3;
+    if (!best.kernel || us < best.us)
+      best = {xt == ZQ_BF16 ? bf16 : f16, 64u * (unsigned)w, ngroups, mgroups,
+              (ngroups + kXcds - 1) / kXcds * kXcds * mgroups, us};
+  };
+#define ZQ_TAKE(MT, NG, W, D, XL, FEW, RATE) \
+  take(&k_dqrows<ZQ_BF16, MT, NG, W, D, XL>, &k_dqrows<ZQ_F16, MT, NG, W, D, XL>, MT, NG, W, FEW, RATE)
+  if (K == 0) return best;
+  if (M <= 16 && M * K * 2 <= kXLds) {
+    // 48 weight rows where N leaves two workgroups a CU or nearly so, else 16
+    // (1 row: N = 24576 27.5 us, 29.0 with 32 weight rows; N = 6144 11.7, 13.0
+    // with 32; N = 2048, K = 2048 5.1, 6.7)
+    if (N >= 16384) ZQ_TAKE(1, 3, 8, 2, true, -1, 45.0);
+    else ZQ_TAKE(1, 1, 8, 6, true, -1, 45.0);
+  } else if (M <= 16) {
+    // (16 rows: N = 24576 33.5 us, 35.5 with 32 weight rows; N = 6144 13.9, 18.1
+    // with 48, 16.5 with 16)
+    if (N >= 16384) ZQ_TAKE(1, 3, 8, 3, false, -1, 45.0);
+    else ZQ_TAKE(1, 2, 16, 2, false, -1, 45.0);
+  } else if (M <= 32) {
+    // (32 rows: N = 24576 38.5 us, 42.5 with 32 weight rows; N = 6144 17.3, 20.9 with 48)
+    if (N >= 16384) ZQ_TAKE(2, 3, 8, 2, false, -1, 45.0);
+    else ZQ_TAKE(2, 2, 8, 2, false, -1, 45.0);
+  } else {
+    // 8 waves where each CU has one workgroup at most, else 4 (128 rows,
+    // N = 8192, K = 2048: 16.4 us, 19.3 with 8; 64 rows, N = K = 6144: 23.9 and 22.8)
+    ZQ_TAKE(4, 2, 8, 2, false, 1, 45.0);
+    ZQ_TAKE(4, 2, 4, 2, false, 0, 45.0);
+    ZQ_TAKE(4, 3, 4, 2, false, -1, 45.0);
+    ZQ_TAKE(4, 4, 4, 2, false, -1, 34.0);
+  }
+#undef ZQ_TAKE
   return best;
 }
 
@@ -744,6 +1003,26 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     return ZQ_E_ALIAS;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const uint16_t* xh = static_cast<const uint16_t*>(x);
+  // the ping-pong kernel's tiles and K splits, up to ZQ_GEMM_HALF_M rows with
+  // 128 x 256 tiles (a K-step of one costs about 0.6 of a 256 x 256 tile's: half
+  // the MFMAs, the same dequantisation)
+  const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK, half = pp && M <= ZQ_GEMM_HALF_M;
+  const int64_t bm = half ? kDqGemmTileM / 2 : kDqGemmTileM;
+  const int64_t mtiles = (M + bm - 1) / bm, ntiles = (N + kDqGemmTileN - 1) / kDqGemmTileN;
+  const int64_t tiles = mtiles * ntiles;
+  double tiled_us = 0.0;
+  const int64_t splits =
+      pp && M > kGemvRows ? large_splits(tiles, K / kDqGemmK, M, N, half ? 0.6 : 1.0, &tiled_us) : 1;
+  // few rows: the kernel that takes K whole, unless K is long against N (fewer
+  // workgroups then, each reading all of a long x: at K >= 4 N the split kernels
+  // are even or faster, 16 rows 44.7 against 44.9 us, 32 rows 52 against 55), and
+  // past 16 rows where its modelled time is the lower
+  const RowsPlan rows = rows_plan(M, N, K, lgB, xt);
+  if (rows.kernel && (M <= kGemvRows ? K < 4 * N : pp && rows.us < tiled_us)) {
+    if (rows.grid > kMaxGrid) return ZQ_E_SIZE;
+    return launch(rows.kernel, (unsigned)rows.grid, rows.threads, st, xh, codes, scales, M, N, K, lgB, y,
+                  (int)rows.ngroups, (int)rows.mgroups);
+  }
   if (M <= kGemvRows) {
     // few tokens: the weight-streaming kernel; the K range per workgroup
     // halves (down to 256) until about kGemvTargetWgs workgroups run
@@ -761,14 +1040,6 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, true> : &k_dqgemv<ZQ_F16, true>, (unsigned)(ngroups * splits),
                   256u, st, xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
   }
-  // the ping-pong kernel, K split where its tiles are few; up to
-  // ZQ_GEMM_HALF_M rows with 128 x 256 tiles (a K-step of one costs about 0.6
-  // of a 256 x 256 tile's: half the MFMAs, the same dequantisation)
-  const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK, half = pp && M <= ZQ_GEMM_HALF_M;
-  const int64_t bm = half ? kDqGemmTileM / 2 : kDqGemmTileM;
-  const int64_t mtiles = (M + bm - 1) / bm, ntiles = (N + kDqGemmTileN - 1) / kDqGemmTileN;
-  const int64_t tiles = mtiles * ntiles;
-  const int64_t splits = pp ? large_splits(tiles, K / kDqGemmK, M, N, half ? 0.6 : 1.0) : 1;
   if (tiles * splits > kMaxGrid) return ZQ_E_SIZE;
   if (splits > 1) {
     const int64_t count = M * N, fill_grid = count / 256 + 1 < 4096 ? count / 256 + 1 : 4096;
