@@ -22,7 +22,8 @@
 //   k_dqgemv     M <= 16 and K >= 4 N: weight streaming with K split over the
 //                grid, codes loaded straight into the operand registers, x
 //                staged in LDS once per K range.
-//   k_dqgemm_pp  the rest: 256 x 256 tiles (128 x 256 up to 128 rows) over 8
+//   k_dqgemm_pp  the rest: 256 x 256 tiles (256 x 192 or 256 x 128 where they
+//                fill the last round better, 128 x 256 up to 128 rows) over 8
 //                waves in a ping-pong schedule, waves w and w + 4 of a SIMD
 //                half a K-step apart (one stores the next tile and reads its
 //                fragments while the other runs its MFMAs, with its loads
@@ -75,12 +76,8 @@ constexpr int64_t kDqGemmPpMaxK = int64_t(1) << 21;  // 32-bit buffer offsets in
 #ifndef ZQ_GEMM_PP_MAX_SPLITS
 #define ZQ_GEMM_PP_MAX_SPLITS 16
 #endif
-// the split model's two costs: one 64-wide K-step of a 256 x 256 tile on one
-// CU, and one atomic addition into y with the GPU's others (measured: a K-step
-// 1.3-1.7 us, atomic additions about 330 G/s)
-#ifndef ZQ_GEMM_PP_STEP_NS
-#define ZQ_GEMM_PP_STEP_NS 1500
-#endif
+// the split model's cost of one atomic addition into y with the GPU's others
+// (measured: about 330 G/s)
 #ifndef ZQ_GEMM_ATOMIC_PS
 #define ZQ_GEMM_ATOMIC_PS 3
 #endif
@@ -333,21 +330,28 @@ __device__ __forceinline__ void phase_end() {
 // tile w mod T (s = w / T) and adds its partial tile into y, which the host
 // has zeroed; used when the tiles alone would leave much of the GPU idle in
 // the last round.
-// TI = 2: 128 x 256 tiles (each wave 64 x 64) for 65-128 rows, where a
-// 256-row tile would multiply zero rows half the time.
-template <int XT, bool SPLIT, int TI = 4>
+// WM = 2, TI = 4, TJ = 2: 256 x 256 tiles (each wave 128 x 64).  TI = 2: 128 x 256
+// tiles (each wave 64 x 64) for up to 128 rows, where a 256-row tile would multiply
+// zero rows half the time.  WM = 4, TI = 2, TJ = 3 or 2: 256 x 192 and 256 x 128
+// tiles (each wave 64 x 96 or 64 x 64), where they fill the GPU's last round better
+// (tile_plan).
+template <int XT, bool SPLIT, int WM = 2, int TI = 4, int TJ = 2>
 __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
                                                   const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
                                                   int lgB, float* __restrict__ y, int64_t mtiles, int64_t ntiles,
                                                   int splits) {
-  constexpr int BM = 64 * TI, BN = 256, WN = 4, NT = 512;
-  constexpr int TJ = 2;                          // 32 x 32 MFMA tiles per wave: TI x 2 (128 or 64 x 64)
-  constexpr int XC = BM * kBK / 8 / NT;          // x chunks per thread and K-step (TI)
-  constexpr int WC = BN * kBK / 16 / NT;         // 2 code chunks per thread and K-step
+  // WM x WN waves, each with TI x TJ MFMA tiles of 32 x 32
+  constexpr int WN = 8 / WM, BM = 32 * TI * WM, BN = 32 * TJ * WN, NT = 512;
+  constexpr int XC = BM * kBK / 8 / NT;          // x chunks per thread and K-step
+  // code chunks per thread and K-step (rows past BN are outside the resource: they
+  // are stored as zeros and never read)
+  constexpr int WC = (BN * kBK / 16 + NT - 1) / NT, BS = WC * NT * 16 / kBK;
   constexpr int XH = XC / 2;                     // x chunks per part
-  static_assert((TI == 4 || TI == 2) && XC == TI && WC == 2, "tile shape");
+  constexpr int MM = 2 * TI * TJ;                // MFMAs per half K-step
+  static_assert(XC == 2 * XH && XH >= 1 && (WC == 1 || WC == 2), "tile shape");
+  static_assert(MM == 16 || MM == 12 || MM == 8, "schedule");
   __shared__ u32x4 As[2][BM * kLDK / 8];
-  __shared__ u32x4 Bs[2][BN * kLDK / 8];
+  __shared__ u32x4 Bs[2][BS * kLDK / 8];
 
   const int64_t T = mtiles * ntiles;
   const int64_t wg = SPLIT ? blockIdx.x % T : blockIdx.x;
@@ -406,15 +410,18 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
 #pragma unroll
     for (int i = XH * P; i < XH * P + XH; ++i)
       xrs[R][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)xoff[i], 2 * k0, 0));
-    wrs[R][P] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, (int)woff[P], k0, 0));
-    const uint32_t si = (woff[P] + (uint32_t)k0) >> lgB;
-    srs[R][P] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sres, (int)(si * 4), 0, 0));
+    if constexpr (P < WC) {
+      wrs[R][P] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, (int)woff[P], k0, 0));
+      const uint32_t si = (woff[P] + (uint32_t)k0) >> lgB;
+      srs[R][P] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sres, (int)(si * 4), 0, 0));
+    }
   };
   // part P of the register tile: its 16 codes become fl(q * s) narrowed to
   // XT in ob (deq), then x's chunks and ob go to LDS buffer `buf` (store)
   uint32_t ob[8];
   auto deq = [&](auto part_c) {
-    constexpr int P = decltype(part_c)::value;
+    constexpr int P = decltype(part_c)::value < WC ? decltype(part_c)::value : 0;
+    if constexpr (decltype(part_c)::value >= WC) return;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t word = wrs[0][P][j >> 1];
@@ -431,9 +438,11 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
       const int c = tid + NT * i;
       As[buf][(c >> 3) * kRow16 + (c & 7)] = xrs[0][i];
     }
-    const int c = tid + NT * P, bi = (c >> 2) * kRow16 + (c & 3) * 2;
-    Bs[buf][bi] = u32x4{ob[0], ob[1], ob[2], ob[3]};
-    Bs[buf][bi + 1] = u32x4{ob[4], ob[5], ob[6], ob[7]};
+    if constexpr (P < WC) {
+      const int c = tid + NT * P, bi = (c >> 2) * kRow16 + (c & 3) * 2;
+      Bs[buf][bi] = u32x4{ob[0], ob[1], ob[2], ob[3]};
+      Bs[buf][bi + 1] = u32x4{ob[4], ob[5], ob[6], ob[7]};
+    }
   };
 
   f32x16_t acc[TI][TJ];
@@ -467,14 +476,14 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
   // the default priority: raising it for the MFMA phase measured 3-8% slower.
   auto mma = [&](auto part_c, auto dq_c) {
     constexpr int P = decltype(part_c)::value;
-    constexpr bool DQ = decltype(dq_c)::value;
+    constexpr bool DQ = decltype(dq_c)::value && P < WC;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = mfma32<XT>(fa[i][s], fb[j][s], acc[i][j]);
-    if constexpr (DQ && TI == 4) {
+    if constexpr (DQ && MM == 16) {
       deq(part_c);
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);  // 4 MFMAs first: the codes may still be arriving
 #pragma unroll
@@ -483,6 +492,15 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
         __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // 4 VALU
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    } else if constexpr (DQ && MM == 12) {
+      deq(part_c);  // the same 40 VALU instructions, 5 after each of 8
+      __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     } else if constexpr (DQ) {
       deq(part_c);  // 8 MFMAs: the same 40 VALU instructions, 8 after each of 5
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
@@ -543,13 +561,13 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
     deq(I0{});
   }
   __syncthreads();
-  if (wm == 1) phase_end();  // the second wave group starts one phase later
+  if (wave >= 4) phase_end();  // the second wave group starts one phase later
   int kt = 0;
 #pragma unroll 1
   for (; kt + 2 < KT; ++kt) kstep(kt, T_{}, T_{});
   if (kt + 1 < KT) kstep(kt++, T_{}, F_{});
   if (kt < KT) kstep(kt, F_{}, F_{});
-  if (wm == 0) phase_end();  // ... and the first one waits for its last phase
+  if (wave < 4) phase_end();  // ... and the first one waits for its last phase
 
 #pragma unroll
   for (int i = 0; i < TI; ++i)
@@ -875,51 +893,63 @@ __global__ void __launch_bounds__(256) k_fill_zero(float* __restrict__ y, int64_
 static_assert(!ZQ_GEMM_PINGPONG || (kDqGemmTileM == 256 && kDqGemmTileN == 256 && kDqGemmThreads == 512), "ping-pong tile");
 static_assert(64 * ZQ_GEMM_WM * ZQ_GEMM_WN == kDqGemmThreads, "launch shape");
 
-// pp: the ping-pong kernel (K <= kDqGemmPpMaxK), with 128-row tiles if half;
-// otherwise the plain 256 x 256 kernel, which never splits K
-DqGemmKernel dqgemm_kernel(int xt, bool split, bool pp, bool half) {
-  if (pp && half) {
-    if (split) return xt == ZQ_BF16 ? &k_dqgemm_pp<ZQ_BF16, true, 2> : &k_dqgemm_pp<ZQ_F16, true, 2>;
-    return xt == ZQ_BF16 ? &k_dqgemm_pp<ZQ_BF16, false, 2> : &k_dqgemm_pp<ZQ_F16, false, 2>;
-  }
-  if (pp) {
-    if (split) return xt == ZQ_BF16 ? &k_dqgemm_pp<ZQ_BF16, true> : &k_dqgemm_pp<ZQ_F16, true>;
-    return xt == ZQ_BF16 ? &k_dqgemm_pp<ZQ_BF16, false> : &k_dqgemm_pp<ZQ_F16, false>;
-  }
-  return xt == ZQ_BF16 ? &k_dqgemm<ZQ_BF16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>
-                       : &k_dqgemm<ZQ_F16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>;
+// The ping-pong kernel's tile shapes: rows and columns of y, the time of one
+// 64-wide K-step of a tile with few CUs busy and with all of them (measured over
+// the layers' GEMMs: 256 x 256 1.2 us in a round of an eighth to a quarter of the
+// CUs, 1.3-1.5 in half to three quarters, 1.75 in full ones; 256 x 192 1.15, 1.28
+// and 1.40-1.48; 256 x 128 0.85, 0.95-1.0 and 1.0-1.14), and its kernels without and
+// with split K.
+struct TileShape {
+  int bm, bn;
+  double step0_us, step1_us;
+  DqGemmKernel whole, split;
+};
+template <int XT>
+const TileShape* tile_shapes() {
+  static const TileShape shapes[] = {
+      {128, 256, 0.9, 0.9, &k_dqgemm_pp<XT, false, 2, 2, 2>, &k_dqgemm_pp<XT, true, 2, 2, 2>},
+      {256, 256, 1.0, 1.75, &k_dqgemm_pp<XT, false>, &k_dqgemm_pp<XT, true>},
+      {256, 192, 0.78, 1.46, &k_dqgemm_pp<XT, false, 4, 2, 3>, &k_dqgemm_pp<XT, true, 4, 2, 3>},
+      {256, 128, 0.85, 1.05, &k_dqgemm_pp<XT, false, 4, 2, 2>, &k_dqgemm_pp<XT, true, 4, 2, 2>},
+  };
+  return shapes;
 }
 
-// K splits for the 256 x 256 tiles.  A tile's workgroup fills a CU (its LDS
-// buffers alone take 147 KB), so the tiles run in rounds of one workgroup per
-// CU, and a last round that is mostly empty idles much of the GPU (72 tiles
-// on 256 CUs use 28% of it).  Splitting K s ways makes s times as many
-// workgroups of 1/s the K-steps, at the price of a zero fill of y and
-// M N s atomic additions; the count taken minimises the modelled time
-//   ceil(tiles s / CUs) ceil(ksteps / s) step  +  [s > 1] M N s atomic
-// (step, atomic: ZQ_GEMM_PP_STEP_NS, ZQ_GEMM_ATOMIC_PS), which splits the
-// GEMMs of a few hundred rows 2-16 ways and leaves full rounds whole.
-int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double step_scale, double* us) {
+// K splits of the ping-pong kernel's tiles, and the modelled time in us.  A
+// tile's workgroup fills a CU (its LDS buffers alone take 110-147 KB), so the
+// tiles run in rounds of one workgroup per CU, and a last round that is mostly
+// empty idles much of the GPU (72 tiles on 256 CUs use 28% of it).  Splitting K s
+// ways makes s times as many workgroups of 1/s the K-steps, at the price of a zero
+// fill of y and M N s atomic additions; the count taken minimises
+//   (full rounds step1 + [a part of one] (step0 + (step1 - step0) part)) ceil(ksteps / s)
+//   + 4, or 9.5 with the fill's launch, + [s > 1] M N s atomic (1/2 + 1/2 CUs / workgroups)
+// where a K-step takes longer the more CUs run (the clock falls under load), and
+// the additions of all rounds but the last overlap the next one's work.  It splits
+// the GEMMs of a few hundred rows 2-16 ways and leaves full rounds whole.
+int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double step0, double step1, double* us) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   const int64_t most = ksteps < kDqGemmMaxSplits ? ksteps : kDqGemmMaxSplits;
-  const double step = ZQ_GEMM_PP_STEP_NS * 1e-9 * step_scale, atomic = ZQ_GEMM_ATOMIC_PS * 1e-12;
+  const double atomic = ZQ_GEMM_ATOMIC_PS * 1e-6;
   auto cost = [&](int64_t s) {
-    const double rounds = (double)((tiles * s + cus - 1) / cus), steps = (double)((ksteps + s - 1) / s);
-    return rounds * steps * step + (s > 1 ? (double)M * (double)N * (double)s * atomic : 0.0);
+    const int64_t full = tiles * s / cus, part = tiles * s % cus;
+    const double rounds =
+        (double)full * step1 + (part ? step0 + (step1 - step0) * (double)part / (double)cus : 0.0);
+    const double alone = full ? (double)cus / (double)(tiles * s) : 1.0;
+    return rounds * (double)((ksteps + s - 1) / s) +
+           (s > 1 ? (double)M * (double)N * (double)s * atomic * (0.5 + 0.5 * alone) + 9.5 : 4.0);
   };
   int64_t best = 1;
-  double best_cost = cost(1);
+  *us = cost(1);
   for (int64_t s = 2; s <= most; ++s) {
     const double c = cost(s);
-    if (c < best_cost) {
+    if (c < *us) {
       best = s;
-      best_cost = c;
+      *us = c;
     }
   }
-  *us = best_cost * 1e6 + (best > 1 ? 9.5 : 4.0);
   return best;
 }
 
@@ -931,6 +961,40 @@ struct RowsPlan {
   int64_t ngroups, mgroups, grid;
   double us;  // modelled time
 };
+
+// The ping-pong kernel's tile shape and K splits for a product, and its modelled
+// time.  Up to 128 rows 128 x 256 tiles; beyond, the shape of 256 rows whose rounds
+// of one tile per CU (with its best split) take the least: narrower tiles cost more
+// per column, but where 256 columns leave a round part empty they fill it (1,024
+// rows, QKV of the 6144-wide layer: 288 tiles 287 us, 384 of 192 columns 254; 256
+// rows, FC1: 96 tiles split in two 114 us, 192 of 128 columns 101).  Once x is beyond
+// the L2s, what narrower tiles read more of it is priced at 20 TB/s (4,096 rows,
+// FC2: 1,086 us with 256 columns, 1,108 with 192).
+struct TilePlan {
+  const TileShape* shape;
+  int64_t mtiles, ntiles, splits;
+  double us;
+};
+TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int xt) {
+  const TileShape* shapes = xt == ZQ_BF16 ? tile_shapes<ZQ_BF16>() : tile_shapes<ZQ_F16>();
+  const bool half = M <= ZQ_GEMM_HALF_M;
+  TilePlan best{};
+  double bytes0 = 0.0;
+  for (int i = half ? 0 : 1; i < (half ? 1 : 4); ++i) {
+    const TileShape& t = shapes[i];
+    TilePlan p{&t, (M + t.bm - 1) / t.bm, (N + t.bn - 1) / t.bn, 1, 0.0};
+    // rows past M multiply zeros, which takes less power (136 rows, FC1 of the
+    // 6144-wide layer: 1.28 us a step against 1.5 at 256 rows; no difference at 128 columns)
+    const double load = i == 1 || i == 2 ? 0.7 + 0.3 * (double)M / (double)(p.mtiles * t.bm) : 1.0;
+    p.splits =
+        large_splits(p.mtiles * p.ntiles, K / kDqGemmK, M, N, load * t.step0_us, load * t.step1_us, &p.us);
+    const double bytes = (double)K * ((double)p.ntiles * (double)M * 2.0 + (double)p.mtiles * (double)N);
+    if (i <= 1) bytes0 = bytes;
+    else if (M * K * 2 > 16 << 20) p.us += (bytes - bytes0) / 20e6;
+    if (!best.shape || p.us < best.us) best = p;
+  }
+  return best;
+}
 
 // Whether and how k_dqrows runs M rows.  Its time is modelled as a launch and the
 // busiest CU's bytes of codes and x at that CU's share of what the L2s deliver:
@@ -1003,22 +1067,15 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     return ZQ_E_ALIAS;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const uint16_t* xh = static_cast<const uint16_t*>(x);
-  // the ping-pong kernel's tiles and K splits, up to ZQ_GEMM_HALF_M rows with
-  // 128 x 256 tiles (a K-step of one costs about 0.6 of a 256 x 256 tile's: half
-  // the MFMAs, the same dequantisation)
-  const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK, half = pp && M <= ZQ_GEMM_HALF_M;
-  const int64_t bm = half ? kDqGemmTileM / 2 : kDqGemmTileM;
-  const int64_t mtiles = (M + bm - 1) / bm, ntiles = (N + kDqGemmTileN - 1) / kDqGemmTileN;
-  const int64_t tiles = mtiles * ntiles;
-  double tiled_us = 0.0;
-  const int64_t splits =
-      pp && M > kGemvRows ? large_splits(tiles, K / kDqGemmK, M, N, half ? 0.6 : 1.0, &tiled_us) : 1;
+  const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK;
+  TilePlan tiled{};
+  if (pp && M > kGemvRows) tiled = tile_plan(M, N, K, xt);
   // few rows: the kernel that takes K whole, unless K is long against N (fewer
   // workgroups then, each reading all of a long x: at K >= 4 N the split kernels
   // are even or faster, 16 rows 44.7 against 44.9 us, 32 rows 52 against 55), and
   // past 16 rows where its modelled time is the lower
   const RowsPlan rows = rows_plan(M, N, K, lgB, xt);
-  if (rows.kernel && (M <= kGemvRows ? K < 4 * N : pp && rows.us < tiled_us)) {
+  if (rows.kernel && (M <= kGemvRows ? K < 4 * N : pp && rows.us < tiled.us)) {
     if (rows.grid > kMaxGrid) return ZQ_E_SIZE;
     return launch(rows.kernel, (unsigned)rows.grid, rows.threads, st, xh, codes, scales, M, N, K, lgB, y,
                   (int)rows.ngroups, (int)rows.mgroups);
@@ -1040,12 +1097,21 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, true> : &k_dqgemv<ZQ_F16, true>, (unsigned)(ngroups * splits),
                   256u, st, xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
   }
-  if (tiles * splits > kMaxGrid) return ZQ_E_SIZE;
-  if (splits > 1) {
+  if (!pp) {
+    const int64_t mtiles = (M + kDqGemmTileM - 1) / kDqGemmTileM, ntiles = (N + kDqGemmTileN - 1) / kDqGemmTileN;
+    if (mtiles * ntiles > kMaxGrid) return ZQ_E_SIZE;
+    return launch(xt == ZQ_BF16 ? &k_dqgemm<ZQ_BF16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>
+                                : &k_dqgemm<ZQ_F16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>,
+                  (unsigned)(mtiles * ntiles), kDqGemmThreads, st, xh, codes, scales, M, N, K, lgB, y, mtiles, ntiles,
+                  1);
+  }
+  const int64_t tiles = tiled.mtiles * tiled.ntiles;
+  if (tiles * tiled.splits > kMaxGrid) return ZQ_E_SIZE;
+  if (tiled.splits > 1) {
     const int64_t count = M * N, fill_grid = count / 256 + 1 < 4096 ? count / 256 + 1 : 4096;
     int rc = launch(&k_fill_zero, (unsigned)fill_grid, 256u, st, y, count);
     if (rc != ZQ_OK) return rc;
   }
-  return launch(dqgemm_kernel(xt, splits > 1, pp, half), (unsigned)(tiles * splits), kDqGemmThreads, st, xh, codes,
-                scales, M, N, K, lgB, y, mtiles, ntiles, (int)splits);
+  return launch(tiled.splits > 1 ? tiled.shape->split : tiled.shape->whole, (unsigned)(tiles * tiled.splits), 512u, st,
+                xh, codes, scales, M, N, K, lgB, y, tiled.mtiles, tiled.ntiles, (int)tiled.splits);
 }

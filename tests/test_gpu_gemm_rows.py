@@ -48,6 +48,20 @@ def test_few_rows_exact(M, N, K, B, dtype):
     assert torch.equal(buf[[0, -1]].view(torch.int32), guard[[0, -1]].view(torch.int32))
 
 
+# the tiled kernel's shapes: 256 x 192 (first two), 256 x 128 (next two), and
+# splits of K over tiles of any of them; ragged rows and columns, blocks whose
+# scales start inside a tile's first row group
+TILES = [(300, 18431, 640, 256), (257, 18432, 320, 1024), (500, 12280, 640, 128), (511, 12289, 192, 32),
+         (400, 6100, 3072, 256), (520, 2050, 4096, 512), (300, 2000, 6144, 64), (900, 4000, 2048, 256),
+         (1030, 2049, 1088, 1024)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,B", TILES)
+def test_tile_shapes_exact(M, N, K, B, dtype):
+    test_few_rows_exact(M, N, K, B, dtype)
+
+
 def test_few_rows_same_bits_twice():
     """Without a split over the grid the sums run in one fixed order."""
     rng = np.random.default_rng(3)
