@@ -618,9 +618,9 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
 //
 // Bound by HBM for the codes up to 4 rows or so (FC1 of the 6144-wide layer at 1
 // row, 151 MB: 34 -> 27.5 us), then by the L2's rate for codes and x together,
-// since every workgroup reads its rows of x: about 10 TB/s (16 rows 45 -> 33.5
-// us, 32 rows 58 -> 38.5, 64 rows 63 -> 51).  Hence the rows per workgroup: many
-// where N leaves enough workgroups (rows_plan).
+// since every workgroup reads its rows of x: about 10 TB/s (16 rows 45 -> 32.5
+// us, 32 rows 58 -> 37.5, 64 rows 63 -> 49).  Hence the rows per workgroup: as many
+// as leave a workgroup for each CU (rows_plan).
 constexpr int kScaleLds = 8192;             // scales a workgroup can stage
 constexpr int kXLds = 49152;                // bytes of x it can
 constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
@@ -662,7 +662,8 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
   const int steps = 2 * mypairs + (odd && pairs % W == wave ? 1 : 0);
   auto kof = [&](int i) { return (((i >> 1) * W + wave) * 2 + (i & 1)) * 64; };
   // LDS: scales, then x; the partial tiles take their place at the end
-  constexpr int PART = W * MT * NG * 256, SF = kScaleLds, XF = XL ? kXLds / 4 : 0;
+  constexpr bool PAIRS = W * MT * NG > 64;  // partial tiles summed in pairs first: half the LDS
+  constexpr int PW = PAIRS ? W / 2 : W, PART = PW * MT * NG * 256, SF = kScaleLds, XF = XL ? kXLds / 4 : 0;
   constexpr int SC = (SF / 4 + 64 * W - 1) / (64 * W), XC = (XF / 4 + 64 * W - 1) / (64 * W);
   static_assert(SC * 64 * W * 4 == SF && XC * 64 * W * 4 == XF, "staging");
   __shared__ float lds[SF + XF > PART ? SF + XF : PART];
@@ -773,17 +774,34 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
 
   // D register e of lane l: row 4 (l / 16) + e, column l % 16
   __syncthreads();
+  auto put = [&](int w) {
 #pragma unroll
-  for (int t = 0; t < MT; ++t)
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
+      for (int g = 0; g < NG; ++g)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) lds[wave * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane] = acc[t][g][e];
+        for (int e = 0; e < 4; ++e) lds[w * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane] = acc[t][g][e];
+  };
+  if constexpr (PAIRS) {
+    if (wave >= PW) put(wave - PW);
+    __syncthreads();
+    if (wave < PW) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[t][g][e] += lds[wave * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane];
+      put(wave);
+    }
+  } else {
+    put(wave);
+  }
   __syncthreads();
   for (int j = threadIdx.x; j < MT * NG * 256; j += 64 * W) {
     float v = lds[j];
 #pragma unroll
-    for (int w = 1; w < W; ++w) v += lds[w * (MT * NG * 256) + j];
+    for (int w = 1; w < PW; ++w) v += lds[w * (MT * NG * 256) + j];
     const int l = j & 63, e = (j >> 6) & 3, tg = j >> 8;
     const int64_t m = m0 + 16 * (tg / NG) + 4 * (l >> 4) + e, n = n0 + 16 * (tg % NG) + (l & 15);
     if (m < M && n < N) y[m * N + n] = v;
@@ -996,14 +1014,18 @@ TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int xt) {
   return best;
 }
 
-// Whether and how k_dqrows runs M rows.  Its time is modelled as a launch and the
+// Whether and how k_dqrows runs M rows.  Each workgroup reads its rows of x once
+// over all of K, so the weight rows per workgroup (16 NG) are as many as leave
+// about one workgroup per CU (N / 256, up to 96): 16 rows, QKV of the 6144-wide
+// layer 32.7 us with 384 workgroups of 48 weight rows, 28.3 with 231 of 80; 64
+// rows 49.5 and 41.  Past 32 rows the candidates' times are modelled as a launch and the
 // busiest CU's bytes of codes and x at that CU's share of what the L2s deliver:
-//   4 us + ceil(workgroups / 256) (16 NG + 32 MT) K / (45 bytes per ns)
-// (measured within 15%: 64 rows, FC1 of the 6144-wide layer 52 against 51 us, QKV
-// 52 against 51, attention output 26 against 23, FC1 of the 2048-wide layer 11.3
-// against 11.4; the workgroup of 64 weight rows keeps fewer loads in flight, 34
-// bytes per ns).  The tiled kernels' model (large_splits) gives 62, 49, 30 and 22
-// there, 63, 50, 28 and 20 measured.
+//   4 us + ceil(workgroups / 256) (16 NG + 32 MT) K / rate
+// rate 45 bytes per ns where several workgroups or 8 waves share a CU, 31-34 for
+// the wide ones (measured: 64 rows, QKV of the 6144-wide layer 41 us, modelled 42;
+// FC1 49, 48; attention output 23, 26; FC1 of the 2048-wide layer 11.5, 11.3).
+// The tiled kernels' model (tile_plan) gives 49, 62, 30 and 22 there, 50, 63, 28
+// and 20 measured.
 RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
   RowsPlan best{};
   auto take = [&](DqRowsKernel bf16, DqRowsKernel f16, int mt, int ng, int w, int few, double rate) {
@@ -1026,14 +1048,18 @@ RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
     if (N >= 16384) ZQ_TAKE(1, 3, 8, 2, true, -1, 45.0);
     else ZQ_TAKE(1, 1, 8, 6, true, -1, 45.0);
   } else if (M <= 16) {
-    // (16 rows: N = 24576 33.5 us, 35.5 with 32 weight rows; N = 6144 13.9, 18.1
-    // with 48, 16.5 with 16)
-    if (N >= 16384) ZQ_TAKE(1, 3, 8, 3, false, -1, 45.0);
-    else ZQ_TAKE(1, 2, 16, 2, false, -1, 45.0);
+    // (2 weight-row tiles at 16 waves where N is small: N = 6144 13.9 us, 16.5 with one)
+    if (N > 20480) ZQ_TAKE(1, 6, 8, 2, false, -1, 34.0);
+    else if (N > 16384) ZQ_TAKE(1, 5, 8, 3, false, -1, 34.0);
+    else if (N > 12288) ZQ_TAKE(1, 4, 8, 2, false, -1, 34.0);
+    else if (N > 8192) ZQ_TAKE(1, 3, 8, 3, false, -1, 34.0);
+    if (!best.kernel) ZQ_TAKE(1, 2, 16, 2, false, -1, 45.0);
   } else if (M <= 32) {
-    // (32 rows: N = 24576 38.5 us, 42.5 with 32 weight rows; N = 6144 17.3, 20.9 with 48)
-    if (N >= 16384) ZQ_TAKE(2, 3, 8, 2, false, -1, 45.0);
-    else ZQ_TAKE(2, 2, 8, 2, false, -1, 45.0);
+    if (N > 20480) ZQ_TAKE(2, 6, 8, 2, false, -1, 34.0);
+    else if (N > 16384) ZQ_TAKE(2, 5, 8, 2, false, -1, 34.0);
+    else if (N > 12288) ZQ_TAKE(2, 4, 8, 2, false, -1, 34.0);
+    else if (N > 8192) ZQ_TAKE(2, 3, 8, 2, false, -1, 34.0);
+    if (!best.kernel) ZQ_TAKE(2, 2, 8, 2, false, -1, 45.0);
   } else {
     // 8 waves where each CU has one workgroup at most, else 4 (128 rows,
     // N = 8192, K = 2048: 16.4 us, 19.3 with 8; 64 rows, N = K = 6144: 23.9 and 22.8)
@@ -1041,6 +1067,8 @@ RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
     ZQ_TAKE(4, 2, 4, 2, false, 0, 45.0);
     ZQ_TAKE(4, 3, 4, 2, false, -1, 45.0);
     ZQ_TAKE(4, 4, 4, 2, false, -1, 34.0);
+    ZQ_TAKE(4, 5, 4, 2, false, -1, 34.0);
+    ZQ_TAKE(4, 6, 4, 1, false, -1, 31.0);
   }
 #undef ZQ_TAKE
   return best;
