@@ -15,12 +15,13 @@
 // / _f16), in an order the hardware fixes.
 //
 // Kernels:
-//   k_dqrows     few rows (M <= 16 and K < 4 N; above, where its modelled time is
+//   k_dqrows     few rows (M <= 16 mostly; above, where its modelled time is
 //                the lowest: up to 32-64 rows of the layer's GEMMs, a few
 //                hundred of smaller ones): weight streaming on 16 x 16 x 32
-//                MFMAs, K taken whole by each workgroup.
-//   k_dqgemv     M <= 16 and K >= 4 N: weight streaming with K split over the
-//                grid, codes loaded straight into the operand registers, x
+//                MFMAs, K taken whole by each workgroup (in a few ranges where
+//                it is long against N).
+//   k_dqgemv     M <= 16 and K >= 4 N, unless k_dqrows with K in a few ranges is
+//                modelled faster: weight streaming with K split over the grid, codes loaded straight into the operand registers, x
 //                staged in LDS once per K range.
 //   k_dqgemm_pp  the rest: 256 x 256 tiles (256 x 192 or 256 x 128 where they
 //                fill the last round better, 128 x 256 up to 128 rows) over 8
@@ -622,19 +623,21 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
 // us, 32 rows 58 -> 37.5, 64 rows 63 -> 49).  Hence the rows per workgroup: as many
 // as leave a workgroup for each CU (rows_plan).
 constexpr int kScaleLds = 8192;             // scales a workgroup can stage
+constexpr int kRangeScales = 64;            // of them a row's, where K is split over the grid
 constexpr int kXLds = 49152;                // bytes of x it can
 constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
 
-template <int XT, int MT, int NG, int W, int D, bool XL>
+template <int XT, int MT, int NG, int W, int D, bool XL, bool KS = false>
 __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
                                                    const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
-                                                   int lgB, float* __restrict__ y, int ngroups, int mgroups) {
+                                                   int lgB, float* __restrict__ y, int ngroups, int mgroups, int ksplits) {
   constexpr int RN = 16 * NG;
-  static_assert(!XL || MT == 1, "x in LDS");
+  static_assert(!XL || (MT == 1 && !KS), "x in LDS");
   // the row groups of x that share weight rows run on one XCD, one after the
   // other (workgroups are dealt to the XCDs round robin)
   const int xcd = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
-  const int ng = idx / mgroups * kXcds + xcd, mg = idx % mgroups;
+  const int per_n = KS ? mgroups * ksplits : mgroups;
+  const int ng = idx / per_n * kXcds + xcd, mg = idx % per_n % mgroups, ks = KS ? idx % per_n / mgroups : 0;
   if (ng >= ngroups) return;
   const int lane = threadIdx.x & 63, r = lane & 15, h = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -656,11 +659,13 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
   const int src4 = (4 * r + h) * 4;  // operand lane (r, h) takes what lane 4 r + h loaded
   auto operand = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(src4, (int)v); };
   // this wave's steps: pairs of them in turn, so that it uses whole 128-byte lines
-  const int ksteps = (int)(K / 64);
-  const int pairs = ksteps / 2, odd = ksteps & 1;
+  // (KS: those of this workgroup's K range, whole pairs of steps from kb on)
+  const int allpairs = (int)(K / 128), pair0 = KS ? (int)((int64_t)ks * allpairs / ksplits) : 0;
+  const int pair1 = KS ? (int)((int64_t)(ks + 1) * allpairs / ksplits) : allpairs;
+  const int kb = pair0 * 128, pairs = pair1 - pair0, odd = pair1 == allpairs ? (int)(K / 64) & 1 : 0;
   const int mypairs = (pairs - wave + W - 1) / W;
   const int steps = 2 * mypairs + (odd && pairs % W == wave ? 1 : 0);
-  auto kof = [&](int i) { return (((i >> 1) * W + wave) * 2 + (i & 1)) * 64; };
+  auto kof = [&](int i) { return kb + (((i >> 1) * W + wave) * 2 + (i & 1)) * 64; };
   // LDS: scales, then x; the partial tiles take their place at the end
   constexpr bool PAIRS = W * MT * NG > 64;  // partial tiles summed in pairs first: half the LDS
   constexpr int PW = PAIRS ? W / 2 : W, PART = PW * MT * NG * 256, SF = kScaleLds, XF = XL ? kXLds / 4 : 0;
@@ -668,13 +673,28 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
   static_assert(SC * 64 * W * 4 == SF && XC * 64 * W * 4 == XF, "staging");
   __shared__ float lds[SF + XF > PART ? SF + XF : PART];
   u32x4* const xlds = reinterpret_cast<u32x4*>(lds + SF);
-  u32x4 sv[SC], xv[XL ? XC : 1];
-  uint32_t soff[NG];
+  u32x4 sv[KS ? 1 : SC], xv[XL ? XC : 1];
+  // KS: row n's scales of the K range at n * kRangeScales, loaded a row per wave
+  constexpr int SR = RN / W;
+  float sr[KS ? SR : 1];
+  uint32_t soff[NG], srow[KS ? NG : 1];
   const int granules = (int)(K / 8), xr = r < M ? r : 0;  // 16-byte pieces of a row of x
+  if constexpr (KS) {
+    static_assert(SR * W == RN && RN * kRangeScales <= kScaleLds, "staging");
 #pragma unroll
-  for (int j = 0; j < SC; ++j)
-    sv[j] = __builtin_bit_cast(
-        u32x4, __builtin_amdgcn_raw_buffer_load_b128(sres, (int)(threadIdx.x + 64 * W * j) * 16, 0, 0));
+    for (int j = 0; j < SR; ++j)
+      sr[j] = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(
+                     sres, (int)(((uint32_t)((wave + W * j) * K + kb) >> lgB) + lane) * 4, 0, 0));
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      srow[g] = (16 * g + r) * kRangeScales - ((uint32_t)((16 * g + r) * K + kb) >> lgB);
+  } else {
+#pragma unroll
+    for (int j = 0; j < SC; ++j)
+      sv[j] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(sres, (int)(threadIdx.x + 64 * W * j) * 16, 0, 0));
+  }
 #pragma unroll
   for (int g = 0; g < NG; ++g) soff[g] = (uint32_t)((16 * g + r) * K + 16 * h);
   if constexpr (XL) {
@@ -726,7 +746,8 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
       u32x4 cf;
 #pragma unroll
       for (int q = 0; q < 4; ++q) cf[q] = operand(cw[d][g][q]);
-      const float scf = lds[(soff[g] + kof(i)) >> lgB];
+      const uint32_t si = (soff[g] + kof(i)) >> lgB;
+      const float scf = lds[KS ? srow[g] + si : si];
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         uint32_t b[4];
@@ -750,8 +771,13 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
     load_x(d, d);
     __builtin_amdgcn_sched_barrier(0);
   }
+  if constexpr (KS) {
 #pragma unroll
-  for (int j = 0; j < SC; ++j) reinterpret_cast<u32x4*>(lds)[threadIdx.x + 64 * W * j] = sv[j];
+    for (int j = 0; j < SR; ++j) lds[(wave + W * j) * kRangeScales + lane] = sr[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < SC; ++j) reinterpret_cast<u32x4*>(lds)[threadIdx.x + 64 * W * j] = sv[j];
+  }
   if constexpr (XL) {
 #pragma unroll
     for (int j = 0; j < XC; ++j) {
@@ -804,7 +830,10 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
     for (int w = 1; w < PW; ++w) v += lds[w * (MT * NG * 256) + j];
     const int l = j & 63, e = (j >> 6) & 3, tg = j >> 8;
     const int64_t m = m0 + 16 * (tg / NG) + 4 * (l >> 4) + e, n = n0 + 16 * (tg % NG) + (l & 15);
-    if (m < M && n < N) y[m * N + n] = v;
+    if (m < M && n < N) {
+      if constexpr (KS) atomicAdd(y + m * N + n, v);
+      else y[m * N + n] = v;
+    }
   }
 }
 
@@ -911,6 +940,10 @@ __global__ void __launch_bounds__(256) k_fill_zero(float* __restrict__ y, int64_
 static_assert(!ZQ_GEMM_PINGPONG || (kDqGemmTileM == 256 && kDqGemmTileN == 256 && kDqGemmThreads == 512), "ping-pong tile");
 static_assert(64 * ZQ_GEMM_WM * ZQ_GEMM_WN == kDqGemmThreads, "launch shape");
 
+int fill_zero(float* y, int64_t count, hipStream_t st) {
+  return launch(&k_fill_zero, (unsigned)(count / 256 + 1 < 4096 ? count / 256 + 1 : 4096), 256u, st, y, count);
+}
+
 // The ping-pong kernel's tile shapes: rows and columns of y, the time of one
 // 64-wide K-step of a tile with few CUs busy and with all of them (measured over
 // the layers' GEMMs: 256 x 256 1.2 us in a round of an eighth to a quarter of the
@@ -972,11 +1005,11 @@ int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double
 }
 
 using DqRowsKernel = void (*)(const uint16_t*, const int8_t*, const float*, int64_t, int64_t, int64_t, int, float*,
-                              int, int);
+                              int, int, int);
 struct RowsPlan {
   DqRowsKernel kernel;  // null: not for these sizes
   unsigned threads;
-  int64_t ngroups, mgroups, grid;
+  int64_t ngroups, mgroups, ksplits, grid;
   double us;  // modelled time
 };
 
@@ -1035,7 +1068,7 @@ RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
     if (few >= 0 && (wgs <= 256) != (few == 1)) return;
     const double us = 4.0 + (double)((wgs + 255) / 256) * (double)((16 * ng + 32 * mt) * K) / rate * 1e-3;
     if (!best.kernel || us < best.us)
-      best = {xt == ZQ_BF16 ? bf16 : f16, 64u * (unsigned)w, ngroups, mgroups,
+      best = {xt == ZQ_BF16 ? bf16 : f16, 64u * (unsigned)w, ngroups, mgroups, 1,
               (ngroups + kXcds - 1) / kXcds * kXcds * mgroups, us};
   };
 #define ZQ_TAKE(MT, NG, W, D, XL, FEW, RATE) \
@@ -1071,6 +1104,33 @@ RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
     ZQ_TAKE(4, 6, 4, 1, false, -1, 31.0);
   }
 #undef ZQ_TAKE
+  if (M > 32) return best;
+  // K long against N leaves few workgroups that take it whole: 96 weight rows and
+  // as many ranges of K as fill the CUs, added into a zeroed y (6144 x 24576: 64
+  // groups of rows, 4 ranges; 16 rows 45.3 us on the weight-streaming kernel that
+  // splits K 24 ways, 36.6; 32 rows 51.8 on the tiled one, 40.9).  The fill and
+  // this kernel start in 12 us; the weight-streaming kernel takes 7 us, its codes
+  // at 5.7 TB/s and its additions.  Past 32 rows the tiled kernel is even.
+  if (M <= 16 && K >= 4 * N) {
+    best = RowsPlan{};
+    best.us = 7.0 + (double)N * (double)K / 5.7e6 + (double)M * (double)N * (double)((K + 1023) / 1024) * 4e-6;
+  }
+  const int mt = M <= 16 ? 1 : 2;
+  const int64_t ngroups = (N + 95) / 96, ks = ngroups <= 128 ? 256 / ngroups : 1;
+  const double us = 12.0 + (double)((96 + 32 * mt) * K) / (double)ks / 34e3 +
+                    (double)M * (double)N * (double)ks * ZQ_GEMM_ATOMIC_PS * 1e-6;
+  if (ks >= 2 && ks <= K / 1024 && ((K / ks + 128) >> lgB) + 2 <= kRangeScales && us < best.us) {
+    best.kernel = xt == ZQ_BF16 ? (mt == 1 ? &k_dqrows<ZQ_BF16, 1, 6, 8, 2, false, true>
+                                           : &k_dqrows<ZQ_BF16, 2, 6, 8, 2, false, true>)
+                                : (mt == 1 ? &k_dqrows<ZQ_F16, 1, 6, 8, 2, false, true>
+                                           : &k_dqrows<ZQ_F16, 2, 6, 8, 2, false, true>);
+    best.threads = 512;
+    best.ngroups = ngroups;
+    best.mgroups = 1;
+    best.ksplits = ks;
+    best.grid = (ngroups + kXcds - 1) / kXcds * kXcds * ks;
+    best.us = us;
+  }
   return best;
 }
 
@@ -1098,15 +1158,17 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
   const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK;
   TilePlan tiled{};
   if (pp && M > kGemvRows) tiled = tile_plan(M, N, K, xt);
-  // few rows: the kernel that takes K whole, unless K is long against N (fewer
-  // workgroups then, each reading all of a long x: at K >= 4 N the split kernels
-  // are even or faster, 16 rows 44.7 against 44.9 us, 32 rows 52 against 55), and
-  // past 16 rows where its modelled time is the lower
+  // few rows: the kernel of few rows where it has a plan, past 16 rows where that
+  // plan's modelled time is the lower
   const RowsPlan rows = rows_plan(M, N, K, lgB, xt);
-  if (rows.kernel && (M <= kGemvRows ? K < 4 * N : pp && rows.us < tiled.us)) {
+  if (rows.kernel && (M <= kGemvRows || (pp && rows.us < tiled.us))) {
     if (rows.grid > kMaxGrid) return ZQ_E_SIZE;
+    if (rows.ksplits > 1) {
+      const int rc = fill_zero(y, M * N, st);
+      if (rc != ZQ_OK) return rc;
+    }
     return launch(rows.kernel, (unsigned)rows.grid, rows.threads, st, xh, codes, scales, M, N, K, lgB, y,
-                  (int)rows.ngroups, (int)rows.mgroups);
+                  (int)rows.ngroups, (int)rows.mgroups, (int)rows.ksplits);
   }
   if (M <= kGemvRows) {
     // few tokens: the weight-streaming kernel; the K range per workgroup
@@ -1119,8 +1181,7 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     if (splits == 1)
       return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, false> : &k_dqgemv<ZQ_F16, false>, (unsigned)ngroups, 256u, st,
                     xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
-    const int64_t count = M * N, fill_grid = count / 256 + 1 < 4096 ? count / 256 + 1 : 4096;
-    int rc = launch(&k_fill_zero, (unsigned)fill_grid, 256u, st, y, count);
+    const int rc = fill_zero(y, M * N, st);
     if (rc != ZQ_OK) return rc;
     return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, true> : &k_dqgemv<ZQ_F16, true>, (unsigned)(ngroups * splits),
                   256u, st, xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
@@ -1136,8 +1197,7 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
   const int64_t tiles = tiled.mtiles * tiled.ntiles;
   if (tiles * tiled.splits > kMaxGrid) return ZQ_E_SIZE;
   if (tiled.splits > 1) {
-    const int64_t count = M * N, fill_grid = count / 256 + 1 < 4096 ? count / 256 + 1 : 4096;
-    int rc = launch(&k_fill_zero, (unsigned)fill_grid, 256u, st, y, count);
+    const int rc = fill_zero(y, M * N, st);
     if (rc != ZQ_OK) return rc;
   }
   return launch(tiled.splits > 1 ? tiled.shape->split : tiled.shape->whole, (unsigned)(tiles * tiled.splits), 512u, st,

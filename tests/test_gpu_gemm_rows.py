@@ -25,7 +25,10 @@ CASES = [(1, 1, 64, 32), (1, 2049, 2048, 256), (2, 6143, 1088, 64), (4, 16385, 1
          (17, 2047, 2048, 256), (24, 16433, 640, 128), (32, 1500, 1984, 512), (31, 16384, 128, 32),
          (33, 2048, 2048, 128), (64, 2049, 1024, 256), (48, 12320, 448, 64), (63, 16390, 1024, 256),
          (65, 1000, 1088, 256), (130, 2065, 960, 128), (256, 2048, 2048, 256), (200, 333, 704, 1024),
-         (16, 64, 4160, 256), (20, 130, 24640, 32), (40, 96, 9600, 32), (1, 300, 24576, 32)]
+         (16, 64, 4160, 256), (20, 130, 24640, 32), (40, 96, 9600, 32), (1, 300, 24576, 32),
+         # K in a few ranges: whole, ragged and odd ones, blocks that straddle rows and ranges
+         (16, 6144, 24576, 256), (9, 6100, 24640, 512), (32, 6144, 24576, 1024), (24, 4111, 16448, 256),
+         (17, 3000, 12352, 512), (30, 2000, 8256, 1024)]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
