@@ -21,8 +21,9 @@
 //                MFMAs, K taken whole by each workgroup (in a few ranges where
 //                it is long against N).
 //   k_dqgemv     M <= 16 and K >= 4 N, unless k_dqrows with K in a few ranges is
-//                modelled faster: weight streaming with K split over the grid, codes loaded straight into the operand registers, x
-//                staged in LDS once per K range.
+//                modelled faster, or a K too long for k_dqrows: weight streaming
+//                with K split over the grid, codes loaded straight into the
+//                operand registers, x staged in LDS once per K range.
 //   k_dqgemm_pp  the rest: 256 x 256 tiles (256 x 192 or 256 x 128 where they
 //                fill the last round better, 128 x 256 up to 128 rows) over 8
 //                waves in a ping-pong schedule, waves w and w + 4 of a SIMD
