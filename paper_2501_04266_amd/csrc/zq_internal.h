@@ -113,9 +113,8 @@ DequantKernel dequant_kernel(int dt, int qbits);
 // Groups per workgroup of the kernel of a level (its launch covers the full
 // blocks in groups of 4 wave tiles): four on large levels of two slices, else
 // one.
-constexpr int fixed_groups(int P) { return P == 2 ? 4 : 1; }
 constexpr int reduce_groups(int P, int block, bool small) {
-  return !small && block >= 64 && block <= 256 ? fixed_groups(P) : 1;
+  return !small && block >= 64 && block <= 256 && P == 2 ? 4 : 1;
 }
 // ydt < 0: INT4 output only; otherwise also the fused dequantisation to ydt
 // (slices in a row only)

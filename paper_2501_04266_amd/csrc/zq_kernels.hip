@@ -523,11 +523,10 @@ __global__ void __launch_bounds__(kDeqThreads) k_dequant(const uint8_t* __restri
 // Per slice and element: one v_cvt_off_f32_i4 (q/16), one multiply by 16*s
 // ((q/16)*(16 s) is the exact real q*s, so the rounded product is fl(q*s)),
 // one add.  16*s is exact unless it overflows (s > 2^123, i.e. inputs above
-// ~7e37); a wave holding such a scale multiplies by 16 first instead.  In the
-// fixed-P kernel the first slice initialises the sum with its product:
-// +0 + x = x for every x but -0, and a -0 sum and a +0 sum requantise to the
-// same code and scale.  Slices are summed in ascending order, exactly as
-// defined.
+// ~7e37); a wave holding such a scale multiplies by 16 first instead.  The
+// first slice initialises the sum with its product: +0 + x = x for every x but
+// -0, and a -0 sum and a +0 sum requantise to the same code and scale.  Slices
+// are summed in ascending order, exactly as defined.
 //
 // YDT >= 0 adds the fused final dequantisation: the requantised codes are
 // turned back into fl(code * s_out) in YDT (the value qgz_dequantize would
@@ -549,7 +548,6 @@ __device__ __forceinline__ int64_t uniform(int64_t v) {
 // conversion to scalar registers hides from the compiler.)
 #define ZQ_GLOBAL __attribute__((address_space(1)))
 typedef uint32_t u32_any __attribute__((aligned(1)));
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 template <int NW>
 __device__ __forceinline__ void load_words_any(const void* base, uint32_t lane_byte, uint32_t (&w)[NW]) {
@@ -559,31 +557,45 @@ __device__ __forceinline__ void load_words_any(const void* base, uint32_t lane_b
   if constexpr (NW == 4) {
     const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32x4_any*>(p));
     w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
-  } else if constexpr (NW == 2) {
-    const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32x2_any*>(p));
-    w[0] = t.x; w[1] = t.y;
   } else {
     static_assert(NW == 1, "words");
     w[0] = __builtin_nontemporal_load(reinterpret_cast<const ZQ_GLOBAL u32_any*>(p));
   }
 }
 
-// A slice's words and scale for one wave tile.
-template <int NW>
+// The slices of one wave tile (up to U): words and scales.  Each slice's scale
+// is loaded right after its words, so that its arithmetic starts when the two are
+// there, and not when the last slice's are (all words first: P = 8, m =
+// 100,663,296, B = 128 takes 86 us in place of 80).  Where a block spans the wave
+// its scale is wave-uniform and a scalar load: a 64-lane load of one word costs the
+// vector memory path as much as a row of them.
+template <int U, int NW>
+struct SliceBatch {
+  uint32_t w[U][NW];
+  float s[U];
+};
+template <int L, int NW>
 __device__ __forceinline__ void load_slice(const uint8_t* bytes, uint32_t lane_byte, const float* scales,
                                            uint32_t lane_scale, uint32_t (&w)[NW], float& s) {
-  uint32_t sw[1];
   load_words_any(bytes, lane_byte, w);
-  load_words_any(scales, 4 * lane_scale, sw);
-  s = u2f(sw[0]);
+  if constexpr (L == 64) {
+    s = *reinterpret_cast<const ZQ_GLOBAL float*>(uniform((int64_t)reinterpret_cast<uintptr_t>(scales)));
+  } else {
+    uint32_t sw[1];
+    load_words_any(scales, 4 * lane_scale, sw);
+    s = u2f(sw[0]);
+  }
 }
 
 // One slice into a lane's sum: acc[k] = fl(acc[k] + fl(q_k * s)) for the E
-// codes of the NW words ww (FIRST: acc[k] = fl(q_k * s)).  KEEP: an empty asm keeps
-// each sum in its branch: the compiler otherwise moves the additions, common
-// to both branches, behind them and behind the following slices, and holds the
-// products of all slices of a batch in registers meanwhile (the any-P kernel:
-// 315 registers, one wave per SIMD, against 125 and four).
+// codes of the NW words ww (FIRST: acc[k] = fl(q_k * s)).  KEEP: an empty asm
+// keeps each slice's additions where they are: the compiler otherwise moves
+// those of a whole loop body behind its last slice and holds all products in
+// registers meanwhile (two batches of 4: 325 registers, one wave per SIMD,
+// against 122 and four).  It stands behind both branches, so that they meet in
+// the products: with the additions inside the branches the 32 sums of a lane
+// were copied between registers at every slice (P = 4, m = 100,663,296, B =
+// 512: 59 us a level, 48 so).
 template <int E, int NW, bool FIRST, bool KEEP = false>
 __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[NW], float sc) {
   const float s16 = sc * 16.0f;
@@ -596,7 +608,6 @@ __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[
       for (int k = 0; k < 8; ++k) {
         const float prod = f[k] * s16;
         acc[8 * j + k] = FIRST ? prod : acc[8 * j + k] + prod;
-        if constexpr (KEEP) asm volatile("" : "+v"(acc[8 * j + k]));
       }
     }
   } else {
@@ -610,6 +621,10 @@ __device__ __forceinline__ void add_slice(float (&acc)[E], const uint32_t (&ww)[
         acc[8 * j + k] = FIRST ? prod : acc[8 * j + k] + prod;
       }
     }
+  }
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int k = 0; k < E; ++k) asm volatile("" : "+v"(acc[k]));
   }
 }
 
@@ -666,12 +681,13 @@ __device__ __forceinline__ void requant_tile(const float (&acc)[E], int64_t blk0
 // and every block of a level smaller than one group): plain arithmetic, the
 // definition as written, sum from +0, one multiply and one add per slice.  A
 // lane owns byte j = lane + 64 i of the block (elements 2j, 2j + 1).  The
-// loads of 8 slices are in flight together (past the end: byte nbytes - 1
-// and slice P - 1 again, unused).
+// loads of U slices are in flight together (past the end: byte nbytes - 1 and
+// slice P - 1 again, unused): 8, fewer where a lane has more than two bytes of each,
+// so that this path does not set the registers of the kernels it is part of.
 template <int B, typename Src>
 __device__ __forceinline__ void reduce_block(const Src& src, int P, int64_t blk, int len, uint8_t* __restrict__ out,
                                              float* __restrict__ sout, void* __restrict__ y, int ydt) {
-  constexpr int I = B > 128 ? B / 128 : 1, U = 8;
+  constexpr int I = B > 128 ? B / 128 : 1, U = I > 2 ? 16 / I : 8;
   const int lane = threadIdx.x & 63;
   const int nbytes = (len + 1) >> 1;
   const int64_t base = blk * B;
@@ -752,28 +768,19 @@ __global__ void __launch_bounds__(64) k_reduce_blocks(Src src, int P, int64_t m,
   reduce_block<B>(src, P, blk, (int)(rest < B ? rest : B), out, sout, y, ydt);
 }
 
-template <int U, int NW>
-struct SliceBatch {
-  uint32_t w[U][NW];
-  float s[U];
-};
-
-// Any slice count.  Slices are loaded U at a time (a batch); with PIPE into two
-// register buffers, the next batch in flight while one is summed.  Every load is
-// unconditional (the last batch loads slice P - 1 again in place of the
-// slices it lacks, and leaves those out of the sum), so the compiler waits for
-// exactly the loads that it needs; branches around loads make it wait for all
-// (P = 3, m = 20,000,000, B = 128: 13.9 -> 11.7 us; P = 5, m = 30,000,000,
-// B = 512: 26.0 -> 21.3 us).  Batches of 3 where 3 divides P, else 4.  Small
-// levels (E = 8) have up to 8 waves per SIMD to overlap instead: one buffer of
-// 8 slices (P = 16, m = 3,000,000, B = 64: 15.7 us with 16 slices behind
-// branches, 10.3 with 16, 9.2 with 8; two buffers of 8: 9.5).
-template <int B, int E, int U, bool PIPE, int YDT, typename Src>
+// Any slice count, by batches of U slices in two register buffers, the loads of
+// the next batch in flight while one is summed.  The first batch takes the slices
+// that U does not divide (1 .. U of them, one copy of its code for each count), so
+// that every other batch is whole, no load is predicated or repeated and the
+// compiler waits for exactly the loads that it needs.  (With a last batch that
+// loads slice P - 1 again in place of those it lacks, P = 9, m = 6,291,456, B =
+// 128 took 11.4 us, 9.6 so.)
+template <int B, int E, int U, int YDT, typename Src>
 __global__ void __launch_bounds__(kThreads) k_reduce(Src src, int P, int64_t nfull, int tail, unsigned tail_wg,
                                                      uint8_t* __restrict__ out, float* __restrict__ sout,
                                                      void* __restrict__ y) {
   constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW;
-  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4), "lane layout");
+  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 4), "lane layout");
   constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();  // dequantised bytes per lane
   __shared__ u32x4 ybuf[YB > 16 ? kThreads * YB / 16 : 1];
   const int lane = threadIdx.x & 63;
@@ -785,66 +792,57 @@ __global__ void __launch_bounds__(kThreads) k_reduce(Src src, int P, int64_t nfu
   const unsigned lane_byte = lane * (E / 2), lane_scale = lane / L;
   const int64_t last = nfull - GB, first = (int64_t)blockIdx.x * GB;
   const int64_t gblk = uniform(first < last ? first : last), blk0 = gblk + wv * BPW;
-  const int nb = (P + U - 1) / U;
+  const int whole = (P - 1) / U, first_n = P - whole * U;  // whole batches after the first one; its slices
 
-  // slices [b*U, b*U + U) of this wave's tile; CLAMP: slice P - 1 in the place
-  // of those past it
-  auto issue = [&](SliceBatch<U, NW>& X, int b, auto clamp) {
+  // N slices from slice p0 on of this wave's tile
+  auto issue = [&](SliceBatch<U, NW>& X, int p0, auto n) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int p = !decltype(clamp)::value || b * U + u < P ? b * U + u : P - 1;
-      load_slice(src.bytes(p) + blk0 * (B / 2), lane_byte, src.scales(p) + blk0, lane_scale, X.w[u], X.s[u]);
-    }
+    for (int u = 0; u < decltype(n)::value; ++u)
+      load_slice<L>(src.bytes(p0 + u) + blk0 * (B / 2), lane_byte, src.scales(p0 + u) + blk0, lane_scale, X.w[u],
+                    X.s[u]);
   };
-  constexpr std::true_type kClamp{};
-  constexpr std::false_type kWhole{};
+  auto next = [&](SliceBatch<U, NW>& X, int b) { issue(X, first_n + b * U, std::integral_constant<int, U>{}); };
   float acc[E];
-#pragma unroll
-  for (int k = 0; k < E; ++k) acc[k] = 0.0f;
   auto sum = [&](const SliceBatch<U, NW>& X) {
 #pragma unroll
     for (int u = 0; u < U; ++u) add_slice<E, NW, false, true>(acc, X.w[u], X.s[u]);
   };
-  auto sum_last = [&](const SliceBatch<U, NW>& X) {
-    add_slice<E, NW, false, true>(acc, X.w[0], X.s[0]);
-#pragma unroll
-    for (int u = 1; u < U; ++u)
-      if ((nb - 1) * U + u < P) add_slice<E, NW, false, true>(acc, X.w[u], X.s[u]);
-  };
 
-  SliceBatch<U, NW> X0;
-  if constexpr (PIPE) {
-    SliceBatch<U, NW> X1;
-    issue(X0, 0, kClamp);
-    int b = 0;
+  SliceBatch<U, NW> X0, X1;
+  auto start = [&](auto n) {
+    issue(X1, 0, n);
+    if (whole > 0) next(X0, 0);
+    add_slice<E, NW, true, true>(acc, X1.w[0], X1.s[0]);
+#pragma unroll
+    for (int u = 1; u < decltype(n)::value; ++u) add_slice<E, NW, false, true>(acc, X1.w[u], X1.s[u]);
+  };
+  static_assert(U == 3 || U == 4 || U == 6, "first batch");
+  if (first_n == 1) start(std::integral_constant<int, 1>{});
+  else if (first_n == 2) start(std::integral_constant<int, 2>{});
+  else if (U == 3 || first_n == 3) start(std::integral_constant<int, 3>{});
+  else if (U == 4 || first_n == 4) start(std::integral_constant<int, U < 4 ? U : 4>{});
+  else if (first_n == 5) start(std::integral_constant<int, U < 5 ? U : 5>{});
+  else start(std::integral_constant<int, U>{});
+  int b = 0;
 #pragma unroll 1
-    for (; b + 2 < nb; b += 2) {
-      issue(X1, b + 1, kWhole);
-      sum(X0);
-      issue(X0, b + 2, kClamp);
-      sum(X1);
-    }
-    if (b + 1 < nb) {
-      issue(X1, b + 1, kClamp);
-      sum(X0);
-      sum_last(X1);
-    } else {
-      sum_last(X0);
-    }
-  } else {
-#pragma unroll 1
-    for (int b = 0; b < nb - 1; ++b) {
-      issue(X0, b, kWhole);
-      sum(X0);
-    }
-    issue(X0, nb - 1, kClamp);
-    sum_last(X0);
+  for (; b + 2 < whole; b += 2) {
+    next(X1, b + 1);
+    sum(X0);
+    next(X0, b + 2);
+    sum(X1);
+  }
+  if (b + 1 < whole) {
+    next(X1, b + 1);
+    sum(X0);
+    sum(X1);
+  } else if (b < whole) {
+    sum(X0);
   }
   requant_tile<B, E, YDT>(acc, blk0, gblk, lane, out, sout, y, ybuf);
 }
 
-// The slice count fixed at compile time (PC = 2, 4 or 8; E = 32 on large
-// levels, E = 8 on small ones).  Same lane layout, arithmetic and order as
+// The slice count fixed at compile time (PC = 1 .. 8; E = 32 on large levels, E =
+// 8 on small ones of 2, 4 and 8 slices).  Same lane layout, arithmetic and order as
 // k_reduce, with all of a tile's slices loaded at once: the compiler waits for
 // each slice's data on its own (s_waitcnt vmcnt(n) counting the loads issued
 // after it), and the sum of slice 0 starts while the others are still
@@ -857,7 +855,7 @@ __global__ void __launch_bounds__(kThreads) k_reduce_p(Src src, int, int64_t nfu
                                                        uint8_t* __restrict__ out, float* __restrict__ sout,
                                                        void* __restrict__ y) {
   constexpr int L = B / E, BPW = 64 / L, NW = E / 8, WPG = kThreads / 64, GB = WPG * BPW, NBUF = TRC > 1 ? 2 : 1;
-  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 2 || NW == 4) && PC >= 1 && TRC >= 1, "lane layout");
+  static_assert(L >= 1 && L <= 64 && (NW == 1 || NW == 4) && PC >= 1 && TRC >= 1, "lane layout");
   constexpr int YB = YDT < 0 ? 0 : E * elem_size<(YDT < 0 ? 0 : YDT)>();
   __shared__ u32x4 ybuf[YB > 16 ? kThreads * YB / 16 : 1];
   const int lane = threadIdx.x & 63;
@@ -870,25 +868,23 @@ __global__ void __launch_bounds__(kThreads) k_reduce_p(Src src, int, int64_t nfu
   const int64_t last = nfull - GB, first = (int64_t)blockIdx.x * (TRC * GB);
   auto group_blk = [&](int t) { return uniform(first + t * GB < last ? first + t * GB : last); };
 
-  uint32_t w[NBUF][PC][NW];
-  float sc[NBUF][PC];
+  SliceBatch<PC, NW> X[NBUF];
   auto issue = [&](int buf, int64_t gblk) {
     const int64_t blk0 = gblk + wv * BPW;
 #pragma unroll
-    for (int p = 0; p < PC; ++p) {
-      load_slice(src.bytes(p) + blk0 * (B / 2), lane_byte, src.scales(p) + blk0, lane_scale, w[buf][p], sc[buf][p]);
-    }
+    for (int p = 0; p < PC; ++p)
+      load_slice<L>(src.bytes(p) + blk0 * (B / 2), lane_byte, src.scales(p) + blk0, lane_scale, X[buf].w[p],
+                    X[buf].s[p]);
   };
 
   issue(0, group_blk(0));
 #pragma unroll
   for (int t = 0; t < TRC; ++t) {
     if (t + 1 < TRC) issue((t + 1) % NBUF, group_blk(t + 1));
-    const int b = t % NBUF;
     float acc[E];
-    add_slice<E, NW, true>(acc, w[b][0], sc[b][0]);
+    add_slice<E, NW, true>(acc, X[t % NBUF].w[0], X[t % NBUF].s[0]);
 #pragma unroll
-    for (int p = 1; p < PC; ++p) add_slice<E, NW, false>(acc, w[b][p], sc[b][p]);
+    for (int p = 1; p < PC; ++p) add_slice<E, NW, false>(acc, X[t % NBUF].w[p], X[t % NBUF].s[p]);
     const int64_t gblk = group_blk(t);
     requant_tile<B, E, YDT>(acc, gblk + wv * BPW, gblk, lane, out, sout, y, ybuf);
   }
@@ -940,22 +936,39 @@ DequantKernel dequant_kernel(int dt, int qbits) {
   return &k_dequant<ZQ_BF16, 4>;
 }
 
-// The reduce kernel of a level: P = 2, 4 and 8 fixed at compile time for B = 64,
-// 128 and 256 (with two slices on large levels a workgroup takes four groups),
-// any other count by batches of U slices.
+// The reduce kernel of a level.  Large levels: the slice count fixed at compile
+// time up to 8 (with two slices at B = 64 .. 256 a workgroup takes four groups),
+// at or above the batches at every count and block size (1 slice, m =
+// 100,663,296, B = 1024: 38.4 us by batches of 4, 23.2 fixed; 3 slices, B = 128:
+// 48 and 39; 7, B = 512: 84 and 71); batches of 4 for 9 to 12 slices, where batches
+// of 3 are up to 4% slower at 50 million elements and more, and of 3 beyond, which
+// are level with them there and faster below (13 slices, m = 20,971,520, B = 128:
+// 28.9 us, 30.1 with 4).  Small levels, which latency binds: 2, 4 and 8 fixed for B
+// = 64 .. 256, else batches of 6 (64 slices, m = 1,048,576: B = 128 12.1 us, 13.4 by
+// single buffers of 8; B = 512 12.3 and 14.8; with two buffers of 8 up to 8% slower
+// at 13 slices and 6 million elements).
 template <int B, int YDT, typename Src>
 static ReduceKernel<Src> reduce_kernel_for(int P, bool small) {
   constexpr int EL = kReduceElems, ES = kReduceElemsSmall;
   if constexpr (B >= 64 && B <= 256) {
-    if (P == 2) return small ? &k_reduce_p<B, ES, 2, 1, YDT, Src> : &k_reduce_p<B, EL, 2, fixed_groups(2), YDT, Src>;
-    if (P == 4) return small ? &k_reduce_p<B, ES, 4, 1, YDT, Src> : &k_reduce_p<B, EL, 4, fixed_groups(4), YDT, Src>;
-    if (P == 8) return small ? &k_reduce_p<B, ES, 8, 1, YDT, Src> : &k_reduce_p<B, EL, 8, fixed_groups(8), YDT, Src>;
+    if (small && P == 2) return &k_reduce_p<B, ES, 2, 1, YDT, Src>;
+    if (small && P == 4) return &k_reduce_p<B, ES, 4, 1, YDT, Src>;
+    if (small && P == 8) return &k_reduce_p<B, ES, 8, 1, YDT, Src>;
   }
   if constexpr (B <= 512) {
-    if (small) return &k_reduce<B, ES, 8, false, YDT, Src>;
+    if (small) return &k_reduce<B, ES, 6, YDT, Src>;
   }
-  if (P % 3 == 0 && P % 4 != 0) return &k_reduce<B, EL, 3, true, YDT, Src>;
-  return &k_reduce<B, EL, 4, true, YDT, Src>;
+  switch (P) {
+    case 1: return &k_reduce_p<B, EL, 1, 1, YDT, Src>;
+    case 2: return &k_reduce_p<B, EL, 2, reduce_groups(2, B, false), YDT, Src>;
+    case 3: return &k_reduce_p<B, EL, 3, 1, YDT, Src>;
+    case 4: return &k_reduce_p<B, EL, 4, 1, YDT, Src>;
+    case 5: return &k_reduce_p<B, EL, 5, 1, YDT, Src>;
+    case 6: return &k_reduce_p<B, EL, 6, 1, YDT, Src>;
+    case 7: return &k_reduce_p<B, EL, 7, 1, YDT, Src>;
+    case 8: return &k_reduce_p<B, EL, 8, 1, YDT, Src>;
+    default: return P <= 12 ? &k_reduce<B, EL, 4, YDT, Src> : &k_reduce<B, EL, 3, YDT, Src>;
+  }
 }
 
 template <int YDT, typename Src>
