@@ -33,7 +33,7 @@
 //                predicated; K split across workgroups where the tiles are
 //                too few to fill the GPU.
 //   k_dqgemm     the same 256 x 256 tiles in a plain two-stage schedule with
-//                64-bit addresses, for K > kDqGemmPpMaxK.
+//                64-bit addresses, for K > kGemmPpMaxK.
 // The tiled kernels use 32 x 32 MFMA tiles, K advancing 64 at a time, LDS
 // rows padded by 16 bytes so that the 16-byte fragment reads of 16
 // consecutive lanes fall in distinct banks.
@@ -43,10 +43,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "zq.h"
 #include "zq_device.h"
+#include "zq_gemm_plan.h"
 #include "zq_host.h"
 
 #pragma clang fp contract(off)
@@ -66,39 +69,9 @@ namespace zq {
 #ifndef ZQ_GEMM_WN
 #define ZQ_GEMM_WN 4
 #endif
-#ifndef ZQ_GEMM_PINGPONG
-#define ZQ_GEMM_PINGPONG 1
-#endif
 constexpr int kDqGemmTileM = ZQ_GEMM_BM;  // rows of y per workgroup
 constexpr int kDqGemmTileN = ZQ_GEMM_BN;  // columns of y per workgroup
-constexpr int kDqGemmK = 64;              // K must be a multiple of this
 constexpr int kDqGemmThreads = 64 * ZQ_GEMM_WM * ZQ_GEMM_WN;
-constexpr int64_t kDqGemmPpMaxK = int64_t(1) << 21;  // 32-bit buffer offsets in the ping-pong kernel
-// K splits of the ping-pong kernel when its tiles leave CUs idle
-#ifndef ZQ_GEMM_PP_MAX_SPLITS
-#define ZQ_GEMM_PP_MAX_SPLITS 16
-#endif
-// the split model's cost of one atomic addition into y with the GPU's others
-// (measured: about 330 G/s)
-#ifndef ZQ_GEMM_ATOMIC_PS
-#define ZQ_GEMM_ATOMIC_PS 3
-#endif
-constexpr int64_t kDqGemmMaxSplits = ZQ_GEMM_PP_MAX_SPLITS;
-// Row ranges of the split kernels: M <= 16 the weight-streaming kernel k_dqgemv;
-// up to ZQ_GEMM_HALF_M rows the ping-pong kernel's 128 x 256 tiles; beyond, its
-// 256 x 256 tiles.  Measured over the layer's four GEMMs in sequence: k_dqgemv
-// 0.11-0.15 ms at 1-16 tokens against 0.17 for the ping-pong kernel; the
-// 128 x 256 tiles 10-14% faster than the 256 x 256 at 65-128
-// rows and slower at 144-224; and both faster than a 64 x 64 few-row tile
-// kernel (since removed) from 24 rows on.
-#ifndef ZQ_GEMM_HALF_M
-#define ZQ_GEMM_HALF_M 128
-#endif
-// the weight-streaming kernel aims at this many workgroups
-#ifndef ZQ_GEMM_GEMV_TARGET
-#define ZQ_GEMM_GEMV_TARGET 1024
-#endif
-constexpr int64_t kGemvTargetWgs = ZQ_GEMM_GEMV_TARGET;
 using DqGemmKernel = void (*)(const uint16_t*, const int8_t*, const float*, int64_t, int64_t, int64_t, int, float*,
                               int64_t, int64_t, int);
 
@@ -121,7 +94,7 @@ constexpr int kRow16 = kLDK / 8;  // the same in 16-byte units
 #define ZQ_GEMM_XCD_MAP 1
 #endif
 constexpr int kGroupM = ZQ_GEMM_GROUP_M;  // tile rows sharing a weight tile in L2
-constexpr int kXcds = 8;
+constexpr int kXcds = kRowsXcds;
 
 // f(integral_constant<int, i>) for i = I .. N - 1
 template <int I, int N, typename F>
@@ -381,7 +354,7 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
   float srs[1][WC];
   // Loads are buffer loads: a wave-uniform resource per operand (base at the
   // tile's first row, size up to the operand's last row in the tile) plus
-  // loop-invariant 32-bit lane offsets (the host keeps K <= kDqGemmPpMaxK, so
+  // loop-invariant 32-bit lane offsets (the host keeps K <= kGemmPpMaxK, so
   // 256 rows of 2 K bytes fit) and the K-step's byte offset in a scalar
   // register.  Rows past M (columns past N) of a ragged edge tile fall
   // outside the resource and read as zero; they only enter outputs that are
@@ -632,12 +605,9 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
 // since every workgroup reads its rows of x: about 10 TB/s (16 rows 45 -> 32.5
 // us, 32 rows 58 -> 37.5, 64 rows 63 -> 49).  Hence the rows per workgroup: as many
 // as leave a workgroup for each CU (rows_plan).
-constexpr int kScaleLds = 8192;             // scales a workgroup can stage
-constexpr int kRangeScales = 64;            // of them a row's, where K is split over the grid
-constexpr int kXLds = 49152;                // bytes of x it can
 constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
 
-template <int XT, int MT, int NG, int W, int D, bool XL, bool KS = false>
+template <int XT, int MT, int NG, int W, int D, bool XL, bool KS>
 __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
                                                    const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
                                                    int lgB, float* __restrict__ y, int ngroups, int mgroups, int ksplits) {
@@ -859,8 +829,6 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
 // used (16 KB per wave), x's rows over the range are staged into LDS once,
 // and the loop has no barrier.  Rows M .. 15 of the x slab, and its columns
 // past the range, are zero.
-constexpr int kGemvRows = 16;   // x rows (M <= kGemvRows)
-constexpr int kGemvKc = 1024;   // longest K range of a workgroup
 
 template <int XT, bool SPLIT>
 __global__ void __launch_bounds__(256) k_dqgemv(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
@@ -947,201 +915,40 @@ __global__ void __launch_bounds__(256) k_fill_zero(float* __restrict__ y, int64_
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) y[i] = 0.0f;
 }
 
-static_assert(!ZQ_GEMM_PINGPONG || (kDqGemmTileM == 256 && kDqGemmTileN == 256 && kDqGemmThreads == 512), "ping-pong tile");
+static_assert(kBK == kGemmKStep && kDqGemmTileM == 256 && kDqGemmTileN == 256, "tiles of the plan");
 static_assert(64 * ZQ_GEMM_WM * ZQ_GEMM_WN == kDqGemmThreads, "launch shape");
 
 int fill_zero(float* y, int64_t count, hipStream_t st) {
   return launch(&k_fill_zero, (unsigned)(count / 256 + 1 < 4096 ? count / 256 + 1 : 4096), 256u, st, y, count);
 }
 
-// The ping-pong kernel's tile shapes: rows and columns of y, the time of one
-// 64-wide K-step of a tile with few CUs busy and with all of them (measured over
-// the layers' GEMMs: 256 x 256 1.2 us in a round of an eighth to a quarter of the
-// CUs, 1.3-1.5 in half to three quarters, 1.75 in full ones; 256 x 192 1.15, 1.28
-// and 1.40-1.48; 256 x 128 0.85, 0.95-1.0 and 1.0-1.14), and its kernels without and
-// with split K.
-struct TileShape {
-  int bm, bn;
-  double step0_us, step1_us;
-  DqGemmKernel whole, split;
-};
-template <int XT>
-const TileShape* tile_shapes() {
-  static const TileShape shapes[] = {
-      {128, 256, 0.9, 0.9, &k_dqgemm_pp<XT, false, 2, 2, 2>, &k_dqgemm_pp<XT, true, 2, 2, 2>},
-      {256, 256, 1.0, 1.75, &k_dqgemm_pp<XT, false>, &k_dqgemm_pp<XT, true>},
-      {256, 192, 0.78, 1.46, &k_dqgemm_pp<XT, false, 4, 2, 3>, &k_dqgemm_pp<XT, true, 4, 2, 3>},
-      {256, 128, 0.85, 1.05, &k_dqgemm_pp<XT, false, 4, 2, 2>, &k_dqgemm_pp<XT, true, 4, 2, 2>},
-  };
-  return shapes;
-}
-
-// K splits of the ping-pong kernel's tiles, and the modelled time in us.  A
-// tile's workgroup fills a CU (its LDS buffers alone take 110-147 KB), so the
-// tiles run in rounds of one workgroup per CU, and a last round that is mostly
-// empty idles much of the GPU (72 tiles on 256 CUs use 28% of it).  Splitting K s
-// ways makes s times as many workgroups of 1/s the K-steps, at the price of a zero
-// fill of y and M N s atomic additions; the count taken minimises
-//   (full rounds step1 + [a part of one] (step0 + (step1 - step0) part)) ceil(ksteps / s)
-//   + 4, or 9.5 with the fill's launch, + [s > 1] M N s atomic (1/2 + 1/2 CUs / workgroups)
-// where a K-step takes longer the more CUs run (the clock falls under load), and
-// the additions of all rounds but the last overlap the next one's work.  It splits
-// the GEMMs of a few hundred rows 2-16 ways and leaves full rounds whole.
-int64_t large_splits(int64_t tiles, int64_t ksteps, int64_t M, int64_t N, double step0, double step1, double* us) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
-  const int64_t most = ksteps < kDqGemmMaxSplits ? ksteps : kDqGemmMaxSplits;
-  const double atomic = ZQ_GEMM_ATOMIC_PS * 1e-6;
-  auto cost = [&](int64_t s) {
-    const int64_t full = tiles * s / cus, part = tiles * s % cus;
-    const double rounds =
-        (double)full * step1 + (part ? step0 + (step1 - step0) * (double)part / (double)cus : 0.0);
-    const double alone = full ? (double)cus / (double)(tiles * s) : 1.0;
-    return rounds * (double)((ksteps + s - 1) / s) +
-           (s > 1 ? (double)M * (double)N * (double)s * atomic * (0.5 + 0.5 * alone) + 9.5 : 4.0);
-  };
-  int64_t best = 1;
-  *us = cost(1);
-  for (int64_t s = 2; s <= most; ++s) {
-    const double c = cost(s);
-    if (c < *us) {
-      best = s;
-      *us = c;
-    }
-  }
-  return best;
-}
-
+// The kernels of the plan's variants and shapes.
 using DqRowsKernel = void (*)(const uint16_t*, const int8_t*, const float*, int64_t, int64_t, int64_t, int, float*,
                               int, int, int);
-struct RowsPlan {
-  DqRowsKernel kernel;  // null: not for these sizes
-  unsigned threads;
-  int64_t ngroups, mgroups, ksplits, grid;
-  double us;  // modelled time
-};
-
-// The ping-pong kernel's tile shape and K splits for a product, and its modelled
-// time.  Up to 128 rows 128 x 256 tiles; beyond, the shape of 256 rows whose rounds
-// of one tile per CU (with its best split) take the least: narrower tiles cost more
-// per column, but where 256 columns leave a round part empty they fill it (1,024
-// rows, QKV of the 6144-wide layer: 288 tiles 287 us, 384 of 192 columns 254; 256
-// rows, FC1: 96 tiles split in two 114 us, 192 of 128 columns 101).  Once x is beyond
-// the L2s, what narrower tiles read more of it is priced at 20 TB/s (4,096 rows,
-// FC2: 1,086 us with 256 columns, 1,108 with 192).
-struct TilePlan {
-  const TileShape* shape;
-  int64_t mtiles, ntiles, splits;
-  double us;
-};
-TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int xt) {
-  const TileShape* shapes = xt == ZQ_BF16 ? tile_shapes<ZQ_BF16>() : tile_shapes<ZQ_F16>();
-  const bool half = M <= ZQ_GEMM_HALF_M;
-  TilePlan best{};
-  double bytes0 = 0.0;
-  for (int i = half ? 0 : 1; i < (half ? 1 : 4); ++i) {
-    const TileShape& t = shapes[i];
-    TilePlan p{&t, (M + t.bm - 1) / t.bm, (N + t.bn - 1) / t.bn, 1, 0.0};
-    // rows past M multiply zeros, which takes less power (136 rows, FC1 of the
-    // 6144-wide layer: 1.28 us a step against 1.5 at 256 rows; no difference at 128 columns)
-    const double load = i == 1 || i == 2 ? 0.7 + 0.3 * (double)M / (double)(p.mtiles * t.bm) : 1.0;
-    p.splits =
-        large_splits(p.mtiles * p.ntiles, K / kDqGemmK, M, N, load * t.step0_us, load * t.step1_us, &p.us);
-    const double bytes = (double)K * ((double)p.ntiles * (double)M * 2.0 + (double)p.mtiles * (double)N);
-    if (i <= 1) bytes0 = bytes;
-    else if (M * K * 2 > 16 << 20) p.us += (bytes - bytes0) / 20e6;
-    if (!best.shape || p.us < best.us) best = p;
-  }
-  return best;
+template <int XT, int... I>
+DqRowsKernel rows_kernel(int kind, std::integer_sequence<int, I...>) {
+  static const DqRowsKernel kernels[] = {
+      &k_dqrows<XT, kRowsVariants[I].mt, kRowsVariants[I].ng, kRowsVariants[I].w, kRowsVariants[I].d,
+                kRowsVariants[I].xl, kRowsVariants[I].ks>...};
+  return kernels[kind];
+}
+template <int XT, bool SPLIT>
+DqGemmKernel tile_kernel(int kind) {
+  static const DqGemmKernel kernels[] = {&k_dqgemm_pp<XT, SPLIT, 2, 2, 2>, &k_dqgemm_pp<XT, SPLIT, 2, 4, 2>,
+                                         &k_dqgemm_pp<XT, SPLIT, 4, 2, 3>, &k_dqgemm_pp<XT, SPLIT, 4, 2, 2>};
+  return kernels[kind];
 }
 
-// Whether and how k_dqrows runs M rows.  Each workgroup reads its rows of x once
-// over all of K, so the weight rows per workgroup (16 NG) are as many as leave
-// about one workgroup per CU (N / 256, up to 96): 16 rows, QKV of the 6144-wide
-// layer 32.7 us with 384 workgroups of 48 weight rows, 28.3 with 231 of 80; 64
-// rows 49.5 and 41.  Past 32 rows the candidates' times are modelled as a launch and the
-// busiest CU's bytes of codes and x at that CU's share of what the L2s deliver:
-//   4 us + ceil(workgroups / 256) (16 NG + 32 MT) K / rate
-// rate 45 bytes per ns where several workgroups or 8 waves share a CU, 31-34 for
-// the wide ones (measured: 64 rows, QKV of the 6144-wide layer 41 us, modelled 42;
-// FC1 49, 48; attention output 23, 26; FC1 of the 2048-wide layer 11.5, 11.3).
-// The tiled kernels' model (tile_plan) gives 49, 62, 30 and 22 there, 50, 63, 28
-// and 20 measured.
-RowsPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int xt) {
-  RowsPlan best{};
-  auto take = [&](DqRowsKernel bf16, DqRowsKernel f16, int mt, int ng, int w, int few, double rate) {
-    if (((16 * ng * K) >> lgB) + 1 > kScaleLds) return;  // its rows' scales have to fit LDS
-    const int64_t ngroups = (N + 16 * ng - 1) / (16 * ng), mgroups = (M + 16 * mt - 1) / (16 * mt);
-    const int64_t wgs = ngroups * mgroups;
-    if (few >= 0 && (wgs <= 256) != (few == 1)) return;
-    const double us = 4.0 + (double)((wgs + 255) / 256) * (double)((16 * ng + 32 * mt) * K) / rate * 1e-3;
-    if (!best.kernel || us < best.us)
-      best = {xt == ZQ_BF16 ? bf16 : f16, 64u * (unsigned)w, ngroups, mgroups, 1,
-              (ngroups + kXcds - 1) / kXcds * kXcds * mgroups, us};
-  };
-#define ZQ_TAKE(MT, NG, W, D, XL, FEW, RATE) \
-  take(&k_dqrows<ZQ_BF16, MT, NG, W, D, XL>, &k_dqrows<ZQ_F16, MT, NG, W, D, XL>, MT, NG, W, FEW, RATE)
-  if (K == 0) return best;
-  if (M <= 16 && M * K * 2 <= kXLds) {
-    // 48 weight rows where N leaves two workgroups a CU or nearly so, else 16
-    // (1 row: N = 24576 27.5 us, 29.0 with 32 weight rows; N = 6144 11.7, 13.0
-    // with 32; N = 2048, K = 2048 5.1, 6.7)
-    if (N >= 16384) ZQ_TAKE(1, 3, 8, 2, true, -1, 45.0);
-    else ZQ_TAKE(1, 1, 8, 6, true, -1, 45.0);
-  } else if (M <= 16) {
-    // (2 weight-row tiles at 16 waves where N is small: N = 6144 13.9 us, 16.5 with one)
-    if (N > 20480) ZQ_TAKE(1, 6, 8, 2, false, -1, 34.0);
-    else if (N > 16384) ZQ_TAKE(1, 5, 8, 3, false, -1, 34.0);
-    else if (N > 12288) ZQ_TAKE(1, 4, 8, 2, false, -1, 34.0);
-    else if (N > 8192) ZQ_TAKE(1, 3, 8, 3, false, -1, 34.0);
-    if (!best.kernel) ZQ_TAKE(1, 2, 16, 2, false, -1, 45.0);
-  } else if (M <= 32) {
-    if (N > 20480) ZQ_TAKE(2, 6, 8, 2, false, -1, 34.0);
-    else if (N > 16384) ZQ_TAKE(2, 5, 8, 2, false, -1, 34.0);
-    else if (N > 12288) ZQ_TAKE(2, 4, 8, 2, false, -1, 34.0);
-    else if (N > 8192) ZQ_TAKE(2, 3, 8, 2, false, -1, 34.0);
-    if (!best.kernel) ZQ_TAKE(2, 2, 8, 2, false, -1, 45.0);
-  } else {
-    // 8 waves where each CU has one workgroup at most, else 4 (128 rows,
-    // N = 8192, K = 2048: 16.4 us, 19.3 with 8; 64 rows, N = K = 6144: 23.9 and 22.8)
-    ZQ_TAKE(4, 2, 8, 2, false, 1, 45.0);
-    ZQ_TAKE(4, 2, 4, 2, false, 0, 45.0);
-    ZQ_TAKE(4, 3, 4, 2, false, -1, 45.0);
-    ZQ_TAKE(4, 4, 4, 2, false, -1, 34.0);
-    ZQ_TAKE(4, 5, 4, 2, false, -1, 34.0);
-    ZQ_TAKE(4, 6, 4, 1, false, -1, 31.0);
-  }
-#undef ZQ_TAKE
-  if (M > 32) return best;
-  // K long against N leaves few workgroups that take it whole: 96 weight rows and
-  // as many ranges of K as fill the CUs, added into a zeroed y (6144 x 24576: 64
-  // groups of rows, 4 ranges; 16 rows 45.3 us on the weight-streaming kernel that
-  // splits K 24 ways, 36.6; 32 rows 51.8 on the tiled one, 40.9).  The fill and
-  // this kernel start in 12 us; the weight-streaming kernel takes 7 us, its codes
-  // at 5.7 TB/s and its additions.  Past 32 rows the tiled kernel is even.
-  if (M <= 16 && K >= 4 * N) {
-    best = RowsPlan{};
-    best.us = 7.0 + (double)N * (double)K / 5.7e6 + (double)M * (double)N * (double)((K + 1023) / 1024) * 4e-6;
-  }
-  const int mt = M <= 16 ? 1 : 2;
-  const int64_t ngroups = (N + 95) / 96, ks = ngroups <= 128 ? 256 / ngroups : 1;
-  const double us = 12.0 + (double)((96 + 32 * mt) * K) / (double)ks / 34e3 +
-                    (double)M * (double)N * (double)ks * ZQ_GEMM_ATOMIC_PS * 1e-6;
-  if (ks >= 2 && ks <= K / 1024 && ((K / ks + 128) >> lgB) + 2 <= kRangeScales && us < best.us) {
-    best.kernel = xt == ZQ_BF16 ? (mt == 1 ? &k_dqrows<ZQ_BF16, 1, 6, 8, 2, false, true>
-                                           : &k_dqrows<ZQ_BF16, 2, 6, 8, 2, false, true>)
-                                : (mt == 1 ? &k_dqrows<ZQ_F16, 1, 6, 8, 2, false, true>
-                                           : &k_dqrows<ZQ_F16, 2, 6, 8, 2, false, true>);
-    best.threads = 512;
-    best.ngroups = ngroups;
-    best.mgroups = 1;
-    best.ksplits = ks;
-    best.grid = (ngroups + kXcds - 1) / kXcds * kXcds * ks;
-    best.us = us;
-  }
-  return best;
+// Compute units of the current device (asked once a device: they do not change).
+int64_t compute_units() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
+  if (dev < kDevices && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  if (dev < kDevices) known[dev].store(cus, std::memory_order_relaxed);
+  return cus;
 }
 
 }  // namespace
@@ -1157,7 +964,7 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
   const int lgB = log2_block(block);
   if (lgB < 0) return ZQ_E_BLOCK;
   if (xt != ZQ_BF16 && xt != ZQ_F16) return ZQ_E_DTYPE;
-  if (K % kDqGemmK != 0) return ZQ_E_SIZE;
+  if (K % kGemmKStep != 0) return ZQ_E_SIZE;
   if (M == 0 || N == 0) return ZQ_OK;
   if (!y || (K > 0 && (!x || !codes || !scales))) return ZQ_E_NULL;
   if (!aligned(x, 16) || !aligned(codes, 16) || !aligned(scales, 4) || !aligned(y, 4)) return ZQ_E_ALIGN;
@@ -1165,51 +972,35 @@ int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const floa
     return ZQ_E_ALIAS;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const uint16_t* xh = static_cast<const uint16_t*>(x);
-  const bool pp = ZQ_GEMM_PINGPONG && K <= kDqGemmPpMaxK;
-  TilePlan tiled{};
-  if (pp && M > kGemvRows) tiled = tile_plan(M, N, K, xt);
-  // few rows: the kernel of few rows where it has a plan, past 16 rows where that
-  // plan's modelled time is the lower
-  const RowsPlan rows = rows_plan(M, N, K, lgB, xt);
-  if (rows.kernel && (M <= kGemvRows || (pp && rows.us < tiled.us))) {
-    if (rows.grid > kMaxGrid) return ZQ_E_SIZE;
-    if (rows.ksplits > 1) {
-      const int rc = fill_zero(y, M * N, st);
-      if (rc != ZQ_OK) return rc;
+  const bool bf16 = xt == ZQ_BF16;
+  const GemmPlan p = gemm_plan(M, N, K, lgB, compute_units());
+  if (p.grid > kMaxGrid) return ZQ_E_SIZE;
+  if (p.splits > 1) {
+    const int rc = fill_zero(y, M * N, st);
+    if (rc != ZQ_OK) return rc;
+  }
+  const unsigned grid = (unsigned)p.grid;
+  switch (p.route) {
+    case GemmRoute::kRows: {
+      constexpr std::make_integer_sequence<int, kRowsKinds> kinds{};
+      return launch(bf16 ? rows_kernel<ZQ_BF16>(p.kind, kinds) : rows_kernel<ZQ_F16>(p.kind, kinds), grid,
+                    64u * (unsigned)kRowsVariants[p.kind].w, st, xh, codes, scales, M, N, K, lgB, y, (int)p.ntiles,
+                    (int)p.mtiles, (int)p.splits);
     }
-    return launch(rows.kernel, (unsigned)rows.grid, rows.threads, st, xh, codes, scales, M, N, K, lgB, y,
-                  (int)rows.ngroups, (int)rows.mgroups, (int)rows.ksplits);
+    case GemmRoute::kGemv:
+      return launch(p.splits > 1 ? bf16 ? &k_dqgemv<ZQ_BF16, true> : &k_dqgemv<ZQ_F16, true>
+                    : bf16       ? &k_dqgemv<ZQ_BF16, false>
+                                 : &k_dqgemv<ZQ_F16, false>,
+                    grid, 256u, st, xh, codes, scales, M, N, K, lgB, y, p.ntiles, (int)p.kc);
+    case GemmRoute::kTiles: {
+      const DqGemmKernel k = p.splits > 1 ? bf16 ? tile_kernel<ZQ_BF16, true>(p.kind) : tile_kernel<ZQ_F16, true>(p.kind)
+                             : bf16       ? tile_kernel<ZQ_BF16, false>(p.kind)
+                                          : tile_kernel<ZQ_F16, false>(p.kind);
+      return launch(k, grid, 512u, st, xh, codes, scales, M, N, K, lgB, y, p.mtiles, p.ntiles, (int)p.splits);
+    }
+    default:
+      return launch(bf16 ? &k_dqgemm<ZQ_BF16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>
+                         : &k_dqgemm<ZQ_F16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>,
+                    grid, kDqGemmThreads, st, xh, codes, scales, M, N, K, lgB, y, p.mtiles, p.ntiles, 1);
   }
-  if (M <= kGemvRows) {
-    // few tokens: the weight-streaming kernel; the K range per workgroup
-    // halves (down to 256) until about kGemvTargetWgs workgroups run
-    const int64_t ngroups = (N + 63) / 64;
-    int64_t kc = kGemvKc;
-    while (kc > 256 && ngroups * ((K + kc - 1) / kc) < kGemvTargetWgs) kc /= 2;
-    const int64_t splits = K > kc ? (K + kc - 1) / kc : 1;
-    if (ngroups * splits > kMaxGrid) return ZQ_E_SIZE;
-    if (splits == 1)
-      return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, false> : &k_dqgemv<ZQ_F16, false>, (unsigned)ngroups, 256u, st,
-                    xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
-    const int rc = fill_zero(y, M * N, st);
-    if (rc != ZQ_OK) return rc;
-    return launch(xt == ZQ_BF16 ? &k_dqgemv<ZQ_BF16, true> : &k_dqgemv<ZQ_F16, true>, (unsigned)(ngroups * splits),
-                  256u, st, xh, codes, scales, M, N, K, lgB, y, ngroups, (int)kc);
-  }
-  if (!pp) {
-    const int64_t mtiles = (M + kDqGemmTileM - 1) / kDqGemmTileM, ntiles = (N + kDqGemmTileN - 1) / kDqGemmTileN;
-    if (mtiles * ntiles > kMaxGrid) return ZQ_E_SIZE;
-    return launch(xt == ZQ_BF16 ? &k_dqgemm<ZQ_BF16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>
-                                : &k_dqgemm<ZQ_F16, kDqGemmTileM, kDqGemmTileN, ZQ_GEMM_WM, ZQ_GEMM_WN>,
-                  (unsigned)(mtiles * ntiles), kDqGemmThreads, st, xh, codes, scales, M, N, K, lgB, y, mtiles, ntiles,
-                  1);
-  }
-  const int64_t tiles = tiled.mtiles * tiled.ntiles;
-  if (tiles * tiled.splits > kMaxGrid) return ZQ_E_SIZE;
-  if (tiled.splits > 1) {
-    const int rc = fill_zero(y, M * N, st);
-    if (rc != ZQ_OK) return rc;
-  }
-  return launch(tiled.splits > 1 ? tiled.shape->split : tiled.shape->whole, (unsigned)(tiles * tiled.splits), 512u, st,
-                xh, codes, scales, M, N, K, lgB, y, tiled.mtiles, tiled.ntiles, (int)tiled.splits);
 }
