@@ -607,7 +607,7 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
 // as leave a workgroup for each CU (rows_plan).
 constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
 
-template <int XT, int MT, int NG, int W, int D, bool XL, bool KS>
+template <int XT, int MT, int NG, int W, int D, bool XL, bool KS, int AS>
 __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
                                                    const float* __restrict__ scales, int64_t M, int64_t N, int64_t K,
                                                    int lgB, float* __restrict__ y, int ngroups, int mgroups, int ksplits) {
@@ -703,11 +703,14 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
         xw[d][t][s] = __builtin_bit_cast(
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)(xoff[t] + 2 * k0 + dead) + 16 * s, 0, 0));
   };
-  f32x4_t acc[MT][NG];
+  // two sets of accumulators take the MFMA steps in turn: chains half as long
+  f32x4_t acc[AS][MT][NG];
 #pragma unroll
-  for (int t = 0; t < MT; ++t)
+  for (int a = 0; a < AS; ++a)
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[t][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) acc[a][t][g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   auto step = [&](int d, int i) {
     u32x4 xf[MT][2];
 #pragma unroll
@@ -739,7 +742,8 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
                              (float)(int32_t)(int8_t)(w >> (sh + 8)) * scf);
         }
 #pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t][g] = mfma16<XT>(xf[t][s], u32x4{b[0], b[1], b[2], b[3]}, acc[t][g]);
+        for (int t = 0; t < MT; ++t)
+          acc[s % AS][t][g] = mfma16<XT>(xf[t][s], u32x4{b[0], b[1], b[2], b[3]}, acc[s % AS][t][g]);
       }
     }
   };
@@ -778,6 +782,12 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
     }
   }
 
+  if constexpr (AS == 2) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) acc[0][t][g] += acc[1][t][g];
+  }
   // D register e of lane l: row 4 (l / 16) + e, column l % 16
   __syncthreads();
   auto put = [&](int w) {
@@ -786,7 +796,7 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
 #pragma unroll
       for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lds[w * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane] = acc[t][g][e];
+        for (int e = 0; e < 4; ++e) lds[w * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane] = acc[0][t][g][e];
   };
   if constexpr (PAIRS) {
     if (wave >= PW) put(wave - PW);
@@ -797,7 +807,7 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
 #pragma unroll
         for (int g = 0; g < NG; ++g)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[t][g][e] += lds[wave * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane];
+          for (int e = 0; e < 4; ++e) acc[0][t][g][e] += lds[wave * (MT * NG * 256) + ((t * NG + g) * 4 + e) * 64 + lane];
       put(wave);
     }
   } else {
@@ -929,7 +939,7 @@ template <int XT, int... I>
 DqRowsKernel rows_kernel(int kind, std::integer_sequence<int, I...>) {
   static const DqRowsKernel kernels[] = {
       &k_dqrows<XT, kRowsVariants[I].mt, kRowsVariants[I].ng, kRowsVariants[I].w, kRowsVariants[I].d,
-                kRowsVariants[I].xl, kRowsVariants[I].ks>...};
+                kRowsVariants[I].xl, kRowsVariants[I].ks, kRowsVariants[I].sets>...};
   return kernels[kind];
 }
 template <int XT, bool SPLIT>

@@ -22,31 +22,40 @@ constexpr int64_t kXLds = 49152;                      // and bytes of x
 constexpr int64_t kRowsXcds = 8;
 
 // k_dqrows' variants: row tiles and weight-row tiles of 16 a workgroup, waves, steps
-// loaded ahead, x staged in LDS, K split over the grid.
+// loaded ahead, x staged in LDS, K split over the grid, accumulator sets.  Two sets
+// cost nothing where memory binds or their registers leave as many workgroups on a
+// CU; else there is a variant of one set too (64 rows, N = K = 2048: 9.0 us with one
+// set, 9.3 with two; 260 rows, N = 6144, K = 2048 in 4 x 4 tiles: 22.3 and 28.4, since
+// one workgroup of them fills a CU's registers and two of the other).
 struct RowsVariant {
   int mt, ng, w, d;
   bool xl, ks;
+  int sets;
 };
 constexpr RowsVariant kRowsVariants[] = {
-    {1, 3, 8, 2, true, false},  {1, 1, 8, 6, true, false},  {1, 6, 8, 2, false, false}, {1, 5, 8, 3, false, false},
-    {1, 4, 8, 2, false, false}, {1, 3, 8, 3, false, false}, {1, 2, 16, 2, false, false}, {2, 6, 8, 2, false, false},
-    {2, 5, 8, 2, false, false}, {2, 4, 8, 2, false, false}, {2, 3, 8, 2, false, false}, {2, 2, 8, 2, false, false},
-    {4, 2, 8, 2, false, false}, {4, 2, 4, 2, false, false}, {4, 3, 4, 2, false, false}, {4, 4, 4, 2, false, false},
-    {4, 5, 4, 2, false, false}, {4, 6, 4, 1, false, false}, {1, 6, 8, 2, false, true},  {2, 6, 8, 2, false, true},
+    {1, 3, 8, 2, true, false, 2},   {1, 1, 8, 6, true, false, 2},  {1, 6, 8, 2, false, false, 1},
+    {1, 5, 8, 3, false, false, 1},  {1, 4, 8, 2, false, false, 1}, {1, 3, 8, 3, false, false, 1},
+    {1, 2, 16, 2, false, false, 2}, {2, 6, 8, 2, false, false, 2}, {2, 5, 8, 2, false, false, 2},
+    {2, 4, 8, 2, false, false, 2},  {2, 3, 8, 2, false, false, 2}, {2, 2, 8, 2, false, false, 1},
+    {2, 2, 8, 2, false, false, 2},  {4, 2, 8, 2, false, false, 1}, {4, 2, 8, 2, false, false, 2},
+    {4, 2, 4, 2, false, false, 1},  {4, 2, 4, 2, false, false, 2}, {4, 3, 4, 2, false, false, 1},
+    {4, 3, 4, 2, false, false, 2},  {4, 4, 4, 2, false, false, 1}, {4, 4, 4, 2, false, false, 2},
+    {4, 5, 4, 2, false, false, 2},  {4, 6, 4, 1, false, false, 2}, {1, 6, 8, 2, false, true, 2},
+    {2, 6, 8, 2, false, true, 2},
 };
 constexpr int kRowsKinds = sizeof(kRowsVariants) / sizeof(kRowsVariants[0]);
 
-// The ping-pong kernel's tile shapes: rows and columns of y, and
+// The ping-pong kernel's tile shapes: rows and columns of y, accumulator sets, and
 // the time of one 64-wide K-step of a tile with few CUs busy and with all of them
 // (measured over the layers' GEMMs: 256 x 256 1.2 us in a round of an eighth to a
 // quarter of the CUs, 1.3-1.5 in half to three quarters, 1.75 in full ones; 256 x 192
 // 1.15, 1.28 and 1.40-1.48; 256 x 128 0.85, 0.95-1.0 and 1.0-1.14).
 struct TileShape {
-  int bm, bn;
+  int bm, bn, sets;
   double step0_us, step1_us;
 };
 constexpr TileShape kTileShapes[] = {
-    {128, 256, 0.9, 0.9}, {256, 256, 1.0, 1.75}, {256, 192, 0.78, 1.46}, {256, 128, 0.85, 1.05}};
+    {128, 256, 2, 0.9, 0.9}, {256, 256, 1, 1.0, 1.75}, {256, 192, 1, 0.78, 1.46}, {256, 128, 2, 0.85, 1.05}};
 
 enum class GemmRoute { kRows, kGemv, kTiles, kPlain };
 struct GemmPlan {
@@ -57,6 +66,13 @@ struct GemmPlan {
   int64_t kc;                       // k_dqgemv: K per range
   double us;                        // modelled time
 };
+
+// What a sum's error grows with: its square is close to proportional to the length
+// K of one accumulator's chain of MFMA additions, plus 8 for each range of K added up
+// in y and 4 for each wave's part added up in LDS (measured against 64 bits, K 960
+// to 28672, every kernel: the 2-norm of the error is 6e-9 times the root of that,
+// within a tenth).
+inline double sum_drift(double k_chain, double ranges, double waves) { return k_chain + 8.0 * ranges + 4.0 * waves; }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // the same of counts below 2^53, as a double: a plan takes some hundred of these, and
@@ -86,9 +102,33 @@ inline int64_t gemv_range(int64_t N, int64_t K) {
   return kc;
 }
 
-// K splits of the ping-pong kernel's tiles, and the modelled time in us.  A
-// tile's workgroup fills a CU (its LDS buffers alone take 110-147 KB), so the
-// tiles run in rounds of one workgroup per CU, and a last round that is mostly empty idles much of the GPU (72 tiles on 256
+// The drift that no plan exceeds (kDriftSlack: by more than a fortieth of the error).
+// Up to 16 rows that of k_dqgemv, beyond that of 256 x 256 tiles (128 x 256 up to
+// 128 rows) with one set of accumulators, split until they fill rounds of CUs at the
+// price of the additions into y: a faster plan that sums longer chains than these is
+// not taken (256 rows, N = 18432, K = 6144 in 256 x 192 tiles of whole K: 108 us and
+// an error of 4.9e-7, where tiles of K split three ways have 2.7e-7).
+constexpr double kDriftSlack = 1.05;
+inline double drift_limit(int64_t M, int64_t N, const KSplits& ks, int64_t cus) {
+  const bool half = M <= kGemmHalfM;
+  const int64_t tiles = ceil_div(M, half ? 128 : 256) * ceil_div(N, 256);
+  const double step = half ? 0.9 : 1.5, added = (double)M * (double)N * kGemmAtomicUs;
+  int64_t best = 1;
+  double best_us = 0.0;
+  for (int64_t s = 1; s <= ks.most; ++s) {
+    const double us = ceil_ratio(tiles * s, cus) * ks.steps[s] * step + (s > 1 ? (double)s * added : 0.0);
+    if (s == 1 || us < best_us) {
+      best = s;
+      best_us = us;
+    }
+  }
+  return kDriftSlack * sum_drift(ks.steps[best] * kGemmKStep, (double)best, 0.0);
+}
+
+// K splits of the ping-pong kernel's tiles, and the modelled time in us (negative:
+// every count exceeds the drift limit).  A tile's workgroup fills a CU (its LDS
+// buffers alone take 110-147 KB), so the tiles run in rounds of one workgroup per
+// CU, and a last round that is mostly empty idles much of the GPU (72 tiles on 256
 // CUs use 28% of it).  Splitting K s ways makes s times as many workgroups of 1/s
 // the K-steps, at the price of a zero fill of y and M N s atomic additions; the
 // count taken minimises
@@ -98,12 +138,13 @@ inline int64_t gemv_range(int64_t N, int64_t K) {
 // the additions of all rounds but the last overlap the next one's work.  It splits
 // the GEMMs of a few hundred rows 2-16 ways and leaves full rounds whole.
 inline int64_t tile_splits(int64_t tiles, const KSplits& ks, int64_t M, int64_t N, int64_t cus, const TileShape& t,
-                           double load, double* us) {
+                           double load, double limit, double* us) {
   const double step0 = load * t.step0_us, step1 = load * t.step1_us, added = (double)M * (double)N * kGemmAtomicUs;
   int64_t best = 1;
   *us = -1.0;
   for (int64_t s = 1; s <= ks.most; ++s) {
     const double steps = ks.steps[s];
+    if (sum_drift(steps * kGemmKStep / t.sets, (double)s, 0.0) > limit) continue;
     const double wgs = (double)(tiles * s), rnds = wgs / (double)cus, full = (double)(int64_t)rnds, part = rnds - full;
     const double rounds = full * step1 + (part > 0.0 ? step0 + (step1 - step0) * part : 0.0);
     const double alone = full > 0.0 ? (double)cus / wgs : 1.0;
@@ -124,7 +165,7 @@ inline int64_t tile_splits(int64_t tiles, const KSplits& ks, int64_t M, int64_t 
 // rows, FC1: 96 tiles split in two 114 us, 192 of 128 columns 101).  Once x is beyond
 // the L2s, what narrower tiles read more of it is priced at 20 TB/s (4,096 rows,
 // FC2: 1,086 us with 256 columns, 1,108 with 192).
-inline GemmPlan tile_plan(int64_t M, int64_t N, int64_t K, const KSplits& ks, int64_t cus) {
+inline GemmPlan tile_plan(int64_t M, int64_t N, int64_t K, const KSplits& ks, int64_t cus, double limit) {
   const bool half = M <= kGemmHalfM;
   GemmPlan best{};
   bool found = false;
@@ -135,7 +176,8 @@ inline GemmPlan tile_plan(int64_t M, int64_t N, int64_t K, const KSplits& ks, in
     // rows past M multiply zeros, which takes less power (136 rows, FC1 of the
     // 6144-wide layer: 1.28 us a step against 1.5 at 256 rows; no difference at 128 columns)
     const double load = i == 1 || i == 2 ? 0.7 + 0.3 * (double)M / (double)(p.mtiles * t.bm) : 1.0;
-    p.splits = tile_splits(p.mtiles * p.ntiles, ks, M, N, cus, t, load, &p.us);
+    p.splits = tile_splits(p.mtiles * p.ntiles, ks, M, N, cus, t, load, limit, &p.us);
+    if (p.us < 0.0) continue;
     const double bytes = (double)K * ((double)p.ntiles * (double)M * 2.0 + (double)p.mtiles * (double)N);
     if (i <= 1) bytes0 = bytes;
     else if (M * K * 2 > 16 << 20) p.us += (bytes - bytes0) / 20e6;
@@ -158,7 +200,7 @@ inline GemmPlan tile_plan(int64_t M, int64_t N, int64_t K, const KSplits& ks, in
 // FC1 49, 48; attention output 23, 26; FC1 of the 2048-wide layer 11.5, 11.3).
 // The tiled kernels' model (tile_plan) gives 49, 62, 30 and 22 there, 50, 63, 28
 // and 20 measured.
-inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus) {
+inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus, double limit) {
   GemmPlan best{};
   best.route = GemmRoute::kRows;
   best.kind = -1;
@@ -166,11 +208,17 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus)
     if (((16 * ng * K) >> lgB) + 1 > kScaleLds) return;  // its rows' scales have to fit LDS
     const int64_t ngroups = ceil_div(N, 16 * ng), mgroups = ceil_div(M, 16 * mt), wgs = ngroups * mgroups;
     if (few >= 0 && (wgs <= cus) != (few == 1)) return;
-    int kind = 0;
-    for (; kind < kRowsKinds; ++kind) {
-      const RowsVariant& v = kRowsVariants[kind];
-      if (v.mt == mt && v.ng == ng && v.w == w && v.xl == xl && !v.ks) break;
+    // the first variant of these tiles whose sums are short enough, of two sets only
+    // where one workgroup a CU is all there are
+    int kind = -1;
+    for (int i = 0; i < kRowsKinds && kind < 0; ++i) {
+      const RowsVariant& v = kRowsVariants[i];
+      if (v.mt == mt && v.ng == ng && v.w == w && v.xl == xl && !v.ks &&
+          sum_drift((double)K / (w * v.sets), 0.0, w) <= limit &&
+          !(mt == 4 && (ng == 3 || ng == 4) && v.sets == 2 && wgs > cus))
+        kind = i;
     }
+    if (kind < 0) return;
     const int64_t xbytes = xl ? 2 * M : 32 * mt;  // of a column of x
     double us = (double)(ceil_div(wgs, cus) * (16 * ng + xbytes) * K) / rate * 1e-3;
     us += 4.0;
@@ -225,6 +273,7 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus)
   int kind = kRowsKinds - 1;
   while (kRowsVariants[kind].mt != mt) --kind;
   if (((K / ks + 128) >> lgB) + 2 <= kRangeScales && 96 * K < (int64_t(1) << 30) &&
+      sum_drift((double)K / (double)(ks * 8 * kRowsVariants[kind].sets), (double)ks, 8.0) <= limit &&
       (!other || us < other_us))
     best = {GemmRoute::kRows, kind, 1, ngroups, ks, ceil_div(ngroups, kRowsXcds) * kRowsXcds * ks, 0, us};
   return best;
@@ -238,7 +287,9 @@ inline GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus)
     GemmPlan gemv{GemmRoute::kGemv, 0, 1, ceil_div(N, 64), 1, 0, gemv_range(N, K), 0.0};
     gemv.splits = K > gemv.kc ? ceil_div(K, gemv.kc) : 1;
     gemv.grid = gemv.ntiles * gemv.splits;
-    const GemmPlan rows = rows_plan(M, N, K, lgB, cus);
+    const double limit =
+        kDriftSlack * sum_drift((double)(gemv.kc < K ? gemv.kc : K), (double)gemv.splits, 0.0);
+    const GemmPlan rows = rows_plan(M, N, K, lgB, cus, limit);
     return rows.kind >= 0 ? rows : gemv;
   }
   if (K > kGemmPpMaxK) {
@@ -247,7 +298,8 @@ inline GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus)
     return {GemmRoute::kPlain, 0, mt, nt, 1, mt * nt, 0, 0.0};
   }
   const KSplits ks = k_splits(K);
-  const GemmPlan rows = rows_plan(M, N, K, lgB, cus), tiles = tile_plan(M, N, K, ks, cus);
+  const double limit = drift_limit(M, N, ks, cus);
+  const GemmPlan rows = rows_plan(M, N, K, lgB, cus, limit), tiles = tile_plan(M, N, K, ks, cus, limit);
   return rows.kind >= 0 && rows.us < tiles.us ? rows : tiles;
 }
 

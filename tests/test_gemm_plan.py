@@ -1,6 +1,7 @@
 """The dequantise-on-load GEMM's plan (csrc/zq_gemm_plan.h, host arithmetic),
 compiled with the host compiler and asked without a GPU: that no plan exceeds
-what its kernels can hold, and the edges of its rules."""
+what its kernels can hold or sums longer chains than the plans it is compared
+with, and the edges of its rules."""
 import os
 import random
 import subprocess
@@ -22,8 +23,8 @@ def plan(tmp_path_factory):
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
         rows = []
         for line in out:
-            name, mt, nt, splits, grid, us = line.split()
-            rows.append((name, int(mt), int(nt), int(splits), int(grid), float(us)))
+            name, mt, nt, splits, grid, us, drift, limit = line.split()
+            rows.append((name, int(mt), int(nt), int(splits), int(grid), float(us), float(drift), float(limit)))
         assert len(rows) == len(shapes)
         return rows
     return ask
@@ -44,7 +45,7 @@ def _shapes(count, seed):
 def test_plans_fit_their_kernels(plan, cus):
     shapes = _shapes(20000, 5) + [(M, N, 64 * k, 1024) for M in (1, 16, 32) for N in (1, 64, 90, 96)
                                   for k in (1 << 14, 40000, 174762, 174763, 1 << 18)]
-    for (M, N, K, B), (name, mt, nt, splits, grid, us) in zip(shapes, plan(shapes, cus)):
+    for (M, N, K, B), (name, mt, nt, splits, grid, us, drift, limit) in zip(shapes, plan(shapes, cus)):
         what = (M, N, K, B, name, splits)
         kind, _, rest = name.partition(":")
         assert 0 < grid < 2 ** 31, what
@@ -75,16 +76,27 @@ def test_plans_fit_their_kernels(plan, cus):
             assert K <= 2 ** 21 and grid == mt * nt * splits, what
 
 
+@pytest.mark.parametrize("cus", [256, 64])
+def test_no_plan_sums_longer_chains(plan, cus):
+    shapes = _shapes(20000, 11)
+    for s, (name, *_, drift, limit) in zip(shapes, plan(shapes, cus)):
+        assert name == "plain" or drift <= limit + 0.051, (s, name, drift, limit)
+    # 256 x 192 tiles of whole K, one set of accumulators, where tiles of 256 columns
+    # would be split: longer chains, not taken
+    (name, _, _, splits, *_), = plan([(260, 18432, 6144, 256)], cus=256)
+    assert name == "tiles:256x256,split" and splits == 3
+
+
 def test_edges(plan):
     # more ranges of K than 1024 allows: as many as it does, not none
     (name, _, _, splits, *_), = plan([(32, 2048, 8192, 256)])
-    assert (name, splits) == ("ranges:2x6,waves8", 8)
+    assert (name, splits) == ("ranges:2x6,waves8,sets2", 8)
     # no plan that takes K whole (its scales do not fit LDS): the ranges are still compared
     (name, *_), = plan([(32, 2048, 16384, 64)])
-    assert name == "ranges:2x6,waves8"
+    assert name == "ranges:2x6,waves8,sets2"
     # the number of compute units reaches both models: as many weight rows a workgroup
     # as leave one workgroup for each
     (few, *_), (many, *_) = plan([(16, 6144, 2048, 256)], cus=64) + plan([(16, 6144, 2048, 256)], cus=256)
-    assert few == "rows:1x6,waves8" and many == "rows:1x2,waves16"
+    assert few == "rows:1x6,waves8" and many == "rows:1x2,waves16,sets2"
     # no columns of K at all
     assert [r[0] for r in plan([(1, 64, 0, 256), (17, 64, 0, 256)])] == ["stream:256", "tiles:128x256"]
