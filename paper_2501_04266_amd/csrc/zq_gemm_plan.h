@@ -204,7 +204,8 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus,
   GemmPlan best{};
   best.route = GemmRoute::kRows;
   best.kind = -1;
-  auto take = [&](int mt, int ng, int w, bool xl, int few, double rate) {
+  // (start: us before the first step)
+  auto take = [&](int mt, int ng, int w, bool xl, int few, double rate, double start = 4.0) {
     if (((16 * ng * K) >> lgB) + 1 > kScaleLds) return;  // its rows' scales have to fit LDS
     const int64_t ngroups = ceil_div(N, 16 * ng), mgroups = ceil_div(M, 16 * mt), wgs = ngroups * mgroups;
     if (few >= 0 && (wgs <= cus) != (few == 1)) return;
@@ -221,7 +222,10 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus,
     if (kind < 0) return;
     const int64_t xbytes = xl ? 2 * M : 32 * mt;  // of a column of x
     double us = (double)(ceil_div(wgs, cus) * (16 * ng + xbytes) * K) / rate * 1e-3;
-    us += 4.0;
+    // the codes at HBM's rate, of which a part of the GPU has its part
+    const double hbm = (double)N * (double)K / 5.5e6 * 256.0 / (double)cus;
+    if (M <= 16 && us < hbm) us = hbm;
+    us += start;
     if (best.kind < 0 || us < best.us)
       best = {GemmRoute::kRows, kind, mgroups, ngroups, 1, ceil_div(ngroups, kRowsXcds) * kRowsXcds * mgroups, 0, us};
   };
@@ -237,7 +241,7 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus,
     // (2 weight-row tiles at 16 waves where N is small: N = 6144 13.9 us, 16.5 with one)
     const int mt = M <= 16 ? 1 : 2;
     if (per_cu > 2) take(mt, (int)(per_cu < 6 ? per_cu : 6), 8, false, -1, 34.0);
-    if (best.kind < 0 && mt == 1) take(1, 2, 16, false, -1, 45.0);
+    if (best.kind < 0 && mt == 1) take(1, 2, 16, false, -1, 37.0, 2.4);
     if (best.kind < 0 && mt == 2) take(2, 2, 8, false, -1, 45.0);
   } else {
     // 8 waves where each CU has one workgroup at most, else 4 (128 rows,
@@ -250,31 +254,24 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus,
     take(4, 6, 4, false, -1, 31.0);
   }
   if (M > 32) return best;
+  if (M <= kGemvRows && K >= 4 * N) best.kind = -1;  // too few workgroups take K whole
   // K long against N leaves few workgroups that take it whole: 96 weight rows and
   // as many ranges of K as fill the CUs (of 1024 at least), added into a zeroed y (6144
-  // x 24576: 64 groups of rows, 4 ranges; 16 rows 45.3 us on the weight-streaming kernel
-  // that splits K 24 ways, 36.6; 32 rows 51.8 on the tiled one, 40.9).  The fill and
-  // this kernel start in 12 us; the weight-streaming kernel takes 7 us, its codes
-  // at 5.7 TB/s and its additions.  Past 32 rows the tiled kernel is even.
-  bool other = best.kind >= 0;
-  double other_us = best.us;
-  if (M <= kGemvRows && K >= 4 * N) {
-    best.kind = -1;
-    other = true;
-    other_us = 7.0 + (double)N * (double)K / 5.7e6 + (double)M * (double)N * (double)ceil_div(K, 1024) * 4e-6;
-  }
+  // x 24576: 64 groups of rows, 4 ranges; 16 rows 48.1 us on the weight-streaming kernel
+  // that splits K 24 ways, 39.0; 32 rows 51.8 on the tiled one, 40.9).  Past 32 rows
+  // the tiled kernel is even.
   const int mt = M <= 16 ? 1 : 2;
   const int64_t ngroups = ceil_div(N, 96);
   int64_t ks = cus / (ceil_div(ngroups, kRowsXcds) * kRowsXcds);  // (a group's ranges run on one XCD)
   if (ks > K / 1024) ks = K / 1024;
   if (ks < 2) return best;
-  const double us = 12.0 + (double)((96 + 32 * mt) * K) / (double)ks / 34e3 +
+  const double us = 5.9 + (double)mt + (double)((96 + 16 * mt) * K) / (double)ks / 22.1e3 +
                     (double)M * (double)N * (double)ks * kGemmAtomicUs;
   int kind = kRowsKinds - 1;
   while (kRowsVariants[kind].mt != mt) --kind;
   if (((K / ks + 128) >> lgB) + 2 <= kRangeScales && 96 * K < (int64_t(1) << 30) &&
       sum_drift((double)K / (double)(ks * 8 * kRowsVariants[kind].sets), (double)ks, 8.0) <= limit &&
-      (!other || us < other_us))
+      (best.kind < 0 || us < best.us))
     best = {GemmRoute::kRows, kind, 1, ngroups, ks, ceil_div(ngroups, kRowsXcds) * kRowsXcds * ks, 0, us};
   return best;
 }
@@ -284,13 +281,17 @@ inline GemmPlan rows_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus,
 // lower).
 inline GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int lgB, int64_t cus) {
   if (M <= kGemvRows) {
+    // the weight-streaming kernel: its launches, its codes and its additions (16 rows
+    // of K = 4096 against N = 2048: 8.6 us, 9.5 on k_dqrows; N = 4096: 12.9 and 9.9)
     GemmPlan gemv{GemmRoute::kGemv, 0, 1, ceil_div(N, 64), 1, 0, gemv_range(N, K), 0.0};
     gemv.splits = K > gemv.kc ? ceil_div(K, gemv.kc) : 1;
     gemv.grid = gemv.ntiles * gemv.splits;
+    gemv.us = 5.6 + ((double)N * (double)K / 4.8e6 + (double)M * (double)N * (double)gemv.splits * 3e-6) *
+                        256.0 / (double)cus;
     const double limit =
         kDriftSlack * sum_drift((double)(gemv.kc < K ? gemv.kc : K), (double)gemv.splits, 0.0);
     const GemmPlan rows = rows_plan(M, N, K, lgB, cus, limit);
-    return rows.kind >= 0 ? rows : gemv;
+    return rows.kind >= 0 && rows.us < gemv.us ? rows : gemv;
   }
   if (K > kGemmPpMaxK) {
     // one plain kernel, 64-bit addresses

@@ -94,6 +94,9 @@ def test_edges(plan):
     # no plan that takes K whole (its scales do not fit LDS): the ranges are still compared
     (name, *_), = plan([(32, 2048, 16384, 64)])
     assert name == "ranges:2x6,waves8,sets2"
+    # K a little below 4 N: the streaming kernel where splitting K over the grid is faster
+    (name, *_), = plan([(16, 2048, 4096, 256)])
+    assert name.startswith("stream:")
     # the number of compute units reaches both models: as many weight rows a workgroup
     # as leave one workgroup for each
     (few, *_), (many, *_) = plan([(16, 6144, 2048, 256)], cus=64) + plan([(16, 6144, 2048, 256)], cus=256)
