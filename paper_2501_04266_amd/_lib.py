@@ -238,7 +238,7 @@ def qgz_reduce_level_gather(packed_slices, scale_slices, m, block=128, packed_ou
         _need(a, f"packed_slices[{p}]", int4_bytes(m), _U8)
         _need(b, f"scale_slices[{p}]", _nsc(m, block), _F32)
         # the library reads the slice addresses on the device and cannot check
-        # them itself: the vector path (m % 32 == 0) loads 16 bytes per lane
+        # them itself: its contract asks for 16-byte alignment where m % 32 == 0
         if m % 32 == 0 and _dev(a, f"packed_slices[{p}]") % 16:
             raise ValueError(f"packed_slices[{p}] must be 16-byte aligned when m % 32 == 0")
         if _dev(b, f"scale_slices[{p}]") % 4:
@@ -272,9 +272,10 @@ def qgz_reduce_level_gather(packed_slices, scale_slices, m, block=128, packed_ou
 
 def qgz_reduce_level_gather_noalloc(packed_slices, scale_slices, m, block, packed_out, scales_out, stream=None):
     """qgz_reduce_level_gather without any device allocation: the slice
-    addresses go to the library in host arrays (it keeps its own device table
-    per GPU), and the caller passes the outputs.  Calls that may overlap on
-    one GPU share that table and must be ordered (one stream)."""
+    addresses go to the library in host arrays, and the caller passes the
+    outputs.  Up to 64 slices the addresses travel as kernel arguments; beyond
+    that through one device table per GPU that the library keeps, so calls of more
+    than 64 slices that may overlap on one GPU must be ordered (one stream)."""
     import ctypes
     P = len(packed_slices)
     if P != len(scale_slices) or P == 0:

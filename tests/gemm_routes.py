@@ -21,7 +21,7 @@ ROUTES = [
     ("rows:4x5,waves4,sets2", 67, 8204, 448, 64), ("rows:4x6,waves4,sets2", 65, 10296, 448, 32),
     ("rows:4x6,waves4,sets2", 63, 24561, 576, 256),
     # the same with K in ranges, added into y
-    ("ranges:1x6,waves8,sets2", 6, 4014, 6208, 512), ("ranges:2x6,waves8,sets2", 23, 1000, 8640, 1024),
+    ("ranges:1x6,waves8,sets2", 15, 3071, 9280, 512), ("ranges:2x6,waves8,sets2", 23, 1000, 8640, 1024),
     # k_dqgemv: longest range of K
     ("stream:256", 7, 4, 64, 64), ("stream:256,split", 16, 64, 4160, 256), ("stream:512,split", 1, 839, 37568, 32),
     ("stream:1024,split", 3, 1987, 31808, 128),

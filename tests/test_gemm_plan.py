@@ -1,12 +1,14 @@
 """The dequantise-on-load GEMM's plan (csrc/zq_gemm_plan.h, host arithmetic),
-compiled with the host compiler and asked without a GPU: that no plan exceeds
-what its kernels can hold or sums longer chains than the plans it is compared
-with, and the edges of its rules."""
+compiled with the host compiler and asked without a GPU: which kernel runs the
+shapes of the GPU tests, that no plan exceeds what its kernels can hold or sums
+longer chains than the plans it is compared with, and the edges of its rules."""
 import os
 import random
 import subprocess
 
 import pytest
+
+from tests.gemm_routes import ROUTES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2501_04266_amd", "csrc")
@@ -28,6 +30,12 @@ def plan(tmp_path_factory):
         assert len(rows) == len(shapes)
         return rows
     return ask
+
+
+def test_gpu_shapes_run_the_kernels_they_name(plan):
+    got = plan([r[1:] for r in ROUTES])
+    wrong = [(want, g[0], s) for (want, *s), g in zip(ROUTES, got) if want != g[0]]
+    assert not wrong, wrong
 
 
 def _shapes(count, seed):

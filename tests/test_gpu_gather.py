@@ -21,8 +21,8 @@ def _slices(P, m, block, seed):
     return out
 
 
-# large (with and without leftover blocks), two-slice, small-level and ragged
-# (generic kernel) launch shapes
+# large and small levels, with whole and leftover groups and a short last block;
+# less than one group (one wave a block)
 CASES = [(1, 128, 4096), (2, 128, (1 << 23) + 4096), (8, 64, 1 << 20), (48, 128, 1179648), (5, 256, 3000),
          (8, 128, (1 << 23) + 4096), (3, 32, 65536 + 64)]
 
@@ -78,7 +78,7 @@ def test_gather_from_views_and_graph_replay():
 
 def test_gather_binding_checks_and_raw_stream():
     """The binding rejects byte slices that are not 16-byte aligned where the
-    vector path needs them (the library cannot read device-resident
+    library's contract asks for it (which cannot read device-resident
     addresses), and a call on a raw stream handle keeps the tables it built
     alive until the kernel has run."""
     P, block, m = 3, 128, 1 << 16

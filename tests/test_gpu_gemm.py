@@ -37,10 +37,11 @@ def _exact_inputs(M, N, K, B, dtype, seed):
     return x, codes, scales
 
 
-# M <= 16: the weight-streaming kernel; 17-128: the ping-pong kernel's
-# 128 x 256 tiles; M > 128: its 256 x 256 tiles; K split when the tiles are
-# few (down to one K-step per split); ragged edges in M and N and 1, 2, 3
-# and 10 K-steps of 64
+# Small products of any number of rows, with ragged edges in M and N and 1, 2,
+# 3, 10 and more K-steps of 64.  Most run the few-row kernel; (1, 1, 64) runs the
+# weight-streaming one, (100, 520, 6144) 128 x 256 tiles and (256, 512, 6144) 256 x
+# 128 tiles, both with K split 16 ways.  (Every variant of every kernel:
+# test_gpu_gemm_routes.py.)
 EXACT = [(1, 1, 64, 256), (37, 100, 192, 32), (17, 70, 320, 64), (40, 300, 1024, 256), (64, 129, 2048, 128),
          (65, 300, 2048, 64), (100, 520, 6144, 256), (127, 257, 192, 32),
          (128, 128, 64, 256), (300, 257, 1024, 128), (129, 383, 640, 64), (256, 512, 6144, 256),
@@ -60,12 +61,10 @@ def test_dequant_gemm_exact(M, N, K, B, dtype):
     assert bad.size == 0, f"{bad.size} of {got.size} differ; first at {np.unravel_index(bad[0], got.shape)}"
 
 
-# M <= 16: the weight-streaming kernel (codes straight into the 16 x 16 x 32
-# MFMA operands, x staged in LDS over K ranges of up to 1024): ragged N, K
-# that ends inside a 256-wide chunk (64, 192, 320, 1088) or inside a
-# workgroup's range (4160), one and several ranges per row group, ranges of
-# 256, 512 (N = 32768) and 1024 (N = 65600), every block size (B = 32: two
-# blocks per 64-code segment)
+# Up to 16 rows: ragged N, every block size (B = 32: two blocks per 64-code
+# segment).  (1, 1, 64) and (16, 64, 4160) run the weight-streaming kernel, whose
+# last range ends inside a 256-wide chunk; the others the few-row kernel, with K of
+# few and of an odd number of K-steps, x staged in LDS and not.
 DECODE = [(1, 1, 64, 32), (2, 70, 192, 64), (7, 129, 320, 128), (15, 1000, 1088, 256), (16, 64, 4160, 1024),
           (16, 4100, 2048, 32), (3, 32768, 960, 512), (16, 65600, 1088, 64)]
 
@@ -95,8 +94,8 @@ def _check_bound(got, x, codes, scales, N, B, dtype, what):
     return float((err / np.maximum(mag, 1e-300)).max())
 
 
-# M <= 16 the weight-streaming kernel, 17-128 the 128 x 256 tiles, larger M
-# the 256 x 256 tiles; all but (1, 128, 64, 32) split K across workgroups
+# Normal values through the few-row kernel, the tiled one and (256, 384, 6144),
+# (64, 256, 24576) and (200, 6144, 24576) tiles that split K across workgroups
 REAL = [(256, 384, 6144, 256), (100, 130, 1024, 64), (64, 256, 24576, 256), (1, 128, 64, 32),
         (16, 24576, 6144, 256), (200, 6144, 24576, 256), (257, 640, 1024, 128), (513, 256, 1024, 256)]
 
@@ -120,8 +119,8 @@ def test_dequant_gemm_split_y_not_16_byte_aligned(M, N, K, shift):
     4, 8 or 12 bytes past a 16-byte boundary (the C ABI asks only 4-byte
     alignment of y), inside a poisoned buffer: the result is exact and no
     float outside y changes.
-    (5, 70, 320) splits K on the weight-streaming path, (40, 100, 1024) on
-    the 128 x 256 tiles, (600, 300, 12288) on the 256 x 256 tiles."""
+    (5, 70, 320) splits K on the weight-streaming kernel, (600, 300, 12288) on
+    256 x 128 tiles; (40, 100, 1024) runs the few-row kernel in one launch."""
     x, codes, scales = _exact_inputs(M, N, K, 256, "bf16", 4 * M + shift)
     want = oracle.qwz_dequant_gemm(x, codes, scales, N, 256, "bf16")
     buf = poisoned(M * N + 8, torch.float32)
@@ -196,10 +195,10 @@ def test_gpt20b_layer_gemms_sampled_rows(gpt20b_layer):
 
 @pytest.mark.parametrize("M", [1, 16, 64, 1024])
 def test_gpt20b_layer_gemms_few_tokens(gpt20b_layer, M):
-    """The same four GEMMs at the token counts of the other kernel paths: the
-    weight-streaming kernel (1, 16), the 128 x 256 tiles with K split (64),
-    the 256 x 256 tiles, split for attention output and FC2 (1024).  Every
-    row up to 32 tokens, else 24 sampled rows."""
+    """The same four GEMMs at the token counts of the other kernels: the few-row
+    kernel (1, 16, 64; FC2 streamed, in ranges of K and on split 128 x 256 tiles) and
+    at 1024 tokens 256 x 192 and 256 x 128 tiles, FC2 on split 256 x 256 ones.
+    Every row up to 32 tokens, else 24 sampled rows."""
     rows = np.arange(M) if M <= 32 else np.unique(
         np.concatenate([[0, M - 1], np.random.default_rng(M).integers(0, M, 22)]))
     _layer_gemms(gpt20b_layer, M, rows)
@@ -208,8 +207,8 @@ def test_gpt20b_layer_gemms_few_tokens(gpt20b_layer, M):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,B", [(600, 300, 12288, 256), (700, 300, 24576, 128)])
 def test_dequant_gemm_large_tiles_split_k(M, N, K, B, dtype):
-    """Few 256 x 256 tiles with a long K: the host splits K across workgroups
-    (16 ways here) that add their partial tiles into a zeroed y.  x = a/4
+    """Few tiles (256 x 128, 256 x 192) with a long K: the host splits K across
+    workgroups (16 ways here) that add their partial tiles into a zeroed y.  x = a/4
     with |a| <= 4 keeps every partial sum a multiple of 2^-9 below 2^15, so
     the result is exact in any order of the additions."""
     rng = np.random.default_rng(M + K)
@@ -254,9 +253,9 @@ def test_dequant_gemm_long_k(K):
 @pytest.mark.parametrize("M", [8, 64, 640])
 def test_dequant_gemm_graph_capture(M):
     """The GEMM only enqueues kernels, so it replays from a HIP graph: the
-    weight-streaming path (M = 8) and the 128 x 256 tiles (M = 64), both
-    split (each also launches its own zero fill), and the 256 x 256 tiles
-    (M = 640); exact inputs make every replay bit-identical."""
+    weight-streaming kernel with its zero fill (M = 8) and the few-row kernel in
+    one launch (M = 64, 640); exact inputs make every replay bit-identical.  (The
+    tiled kernel, split and whole: test_route_graph_capture.)"""
     N, K, B = 384, 2048, 256
     x, codes, scales = _exact_inputs(M, N, K, B, "bf16", 31 + M)
     xd, cd, sd = _x_dev(x, "bf16"), to_dev(codes), to_dev(scales)

@@ -6,7 +6,9 @@ Row counts at the edges of 16-, 32- and 64-row groups and over one; weight rows
 that do not fill a workgroup of 16, 32, 48 or 64; K of fewer steps than waves,
 an odd number of them, and of several rounds; x small enough to be staged whole
 and not; every block size, with as many scales as can be staged and more (the
-split kernels take those); K >= 4 N, where K is split over the grid.
+split kernels take those); K >= 4 N, where K is split over the grid (the
+weight-streaming kernel, the few-row kernel with K in ranges, and for (40, 96,
+9600) 128 x 256 tiles).
 """
 import numpy as np
 import pytest
@@ -51,9 +53,10 @@ def test_few_rows_exact(M, N, K, B, dtype):
     assert torch.equal(buf[[0, -1]].view(torch.int32), guard[[0, -1]].view(torch.int32))
 
 
-# the tiled kernel's shapes: 256 x 192 (first two), 256 x 128 (next two), and
-# splits of K over tiles of any of them; ragged rows and columns, blocks whose
-# scales start inside a tile's first row group
+# the tiled kernel's shapes: 256 x 192 (first two), 256 x 128 (next two), with K
+# split in two (fifth) and (900, 4000, 2048); ragged rows and columns, blocks whose
+# scales start inside a tile's first row group.  The other three run the few-row
+# kernel's wide variants.  (Every shape, whole and split: test_gpu_gemm_routes.py.)
 TILES = [(300, 18431, 640, 256), (257, 18432, 320, 1024), (500, 12280, 640, 128), (511, 12289, 192, 32),
          (400, 6100, 3072, 256), (520, 2050, 4096, 512), (300, 2000, 6144, 64), (900, 4000, 2048, 256),
          (1030, 2049, 1088, 1024)]

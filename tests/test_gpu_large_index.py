@@ -46,7 +46,7 @@ def test_qgz_beyond_2g_elements():
 
 def test_reduce_level_beyond_2g_elements():
     """P = 2 random slices of m = 2^31 + 4096 elements (ragged: the last
-    blocks fall outside whole tile groups), reduced and also fused with the
+    group moved back over its neighbour), reduced and also fused with the
     final dequantisation to bf16."""
     P, m, block = 2, (1 << 31) + 4096, 128
     nb4, nsc = (m + 1) // 2, (m + block - 1) // block

@@ -186,8 +186,8 @@ for P in (1, 2, 3, 4, 8, 48):
 for P, block, m in ((3, 128, (1 << 23) + 4096), (2, 64, (1 << 23) + 2048), (2, 256, (1 << 24) + 256),
                     (1, 128, (1 << 23) + 4096), (2, 32, (1 << 22) + 1024)):
     REDUCE_CASES.append((P, block, m))
-# batches that do not divide P (odd job counts in the pipelined kernel), and
-# the largest P the ABI accepts, on the small-level and the generic path
+# batches that do not divide P (a short first batch), and the largest P the ABI
+# accepts, on a small level and on one of less than a group
 for P, block, m in ((5, 128, (1 << 23) + 4096), (9, 64, 1 << 23), (17, 128, 4096 * 8),
                     (1024, 128, 8192), (1024, 64, 1000)):
     REDUCE_CASES.append((P, block, m))
@@ -425,9 +425,8 @@ def test_concurrent_host_threads_on_separate_streams():
 # Inputs that reach the reduce level's rare branches (tests/pin_checks.py,
 # special_reduce_slices): non-zero block sums below the 2^-119 flush
 # threshold (with subnormal products), and slice scales above 2^124, for
-# which 16 * s is not finite.  Each on the large (P >= 3), two-slice
-# (P <= 2) and small-level vector shapes and on the per-block generic kernel
-# (ragged m, and the leftover blocks after the last whole group).
+# which 16 * s is not finite.  Each on large and small levels, on levels of less
+# than a group (one wave a block) and with short last blocks.
 SPECIAL_REDUCE_CASES = [
     ("subthreshold", 2, 128, (1 << 23) + 4096),
     ("subthreshold", 3, 128, (1 << 23) + 4096),
@@ -487,8 +486,8 @@ def test_reduce_edge_sums(kind, P, block, m):
 # at sizes where the workgroups take T = 4 groups (P = 2) and the group count
 # leaves 1, 2 or 3 over, so the last workgroup clamps to the last group and
 # recomputes it; on small levels (8 elements per lane, one group per
-# workgroup) from one group up.  Some sizes also leave a block for the
-# generic kernel.  Plain, fused (f32, bf16) and gathered.
+# workgroup) from one group up.  Some sizes also leave blocks after the last
+# whole group.  Plain, fused (f32, bf16) and gathered.
 FIXED_P_CASES = [(2, 128, 8192 * 4097), (2, 128, 8192 * 4098 + 128), (2, 256, 8192 * 4099),
                  (2, 64, 8192 * 4097 + 64), (4, 64, 8192 * 4098), (4, 256, 8192 * 4099),
                  (8, 64, 8192 * 4098), (8, 256, 8192 * 4097),

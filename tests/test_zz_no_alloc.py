@@ -3,7 +3,8 @@
 arrays of slice addresses, against the existing gathered reduce
 (qgz_reduce_level_gather, device tables) and the oracle.  Several calls in
 a row, each smaller than the one before, so a call that read a stale entry
-of the shared device table left by a larger earlier call would fail."""
+of the device table (more than 64 slices) left by a larger earlier call would
+fail."""
 import ctypes
 
 import numpy as np
@@ -38,7 +39,7 @@ def _noalloc(packed, scales, m, block, po, so):
 
 
 # (P, m, block) in order of decreasing input size: the largest P the table
-# holds; a large level on the vector path; a ragged level (generic kernel)
+# holds; a level whose addresses travel as kernel arguments; a ragged one
 CALLS = [(1024, 16384, 128), (8, (1 << 20) + 4096, 128), (3, 65536 + 77, 64)]
 
 
