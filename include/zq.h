@@ -194,9 +194,9 @@ int qgz_reduce_level_gather_noalloc(const uint8_t* const* packed_slices, const f
  * must not overlap an input.  Other conventions as above.
  * When to use it: on MI355X this call is faster than qwz_dequantize of the
  * layer followed by a library bf16 GEMM (hipBLASLt) up to about 1,000 rows of
- * x (GPT-20B layer's four GEMMs: 0.15 against 0.53 ms at 16 rows, 0.22 against
- * 0.53 ms at 64, about 1.05 against 1.15 ms at 1,024).  With many more rows
- * the separate path wins (6.1 against 5.2 ms at 8,192), so large batches
+ * x (GPT-20B layer's four GEMMs: 0.12 against 0.54 ms at 16 rows, 0.19 against
+ * 0.52 ms at 64, 1.00 against 1.15 ms at 1,024).  With many more rows
+ * the separate path wins (6.0 against 5.2 ms at 8,192), so large batches
  * should dequantise the gathered layer once and call a library GEMM. */
 int qwz_dequant_gemm(const void* x, zq_dtype xt, const int8_t* codes, const float* scales, int64_t M, int64_t N,
                      int64_t K, int32_t block, float* y, void* stream);

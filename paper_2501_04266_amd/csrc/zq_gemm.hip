@@ -20,10 +20,10 @@
 //                hundred of smaller ones): weight streaming on 16 x 16 x 32
 //                MFMAs, K taken whole by each workgroup (in a few ranges where
 //                it is long against N).
-//   k_dqgemv     M <= 16 and K >= 4 N, unless k_dqrows with K in a few ranges is
-//                modelled faster, or a K too long for k_dqrows: weight streaming
-//                with K split over the grid, codes loaded straight into the
-//                operand registers, x staged in LDS once per K range.
+//   k_dqgemv     M <= 16 where it is modelled faster (K long against N, few weight
+//                rows) or K is too long for k_dqrows: weight streaming with K split
+//                over the grid, codes loaded straight into the operand registers,
+//                x staged in LDS once per K range.
 //   k_dqgemm_pp  the rest: 256 x 256 tiles (256 x 192 or 256 x 128 where they
 //                fill the last round better, 128 x 256 up to 128 rows) over 8
 //                waves in a ping-pong schedule, waves w and w + 4 of a SIMD
@@ -34,6 +34,7 @@
 //                too few to fill the GPU.
 //   k_dqgemm     the same 256 x 256 tiles in a plain two-stage schedule with
 //                64-bit addresses, for K > kGemmPpMaxK.
+// Which of them runs a product, and how, is gemm_plan's (zq_gemm_plan.h).
 // The tiled kernels use 32 x 32 MFMA tiles, K advancing 64 at a time, LDS
 // rows padded by 16 bytes so that the 16-byte fragment reads of 16
 // consecutive lanes fall in distinct banks.
@@ -359,7 +360,7 @@ __global__ void __launch_bounds__(512) k_dqgemm_pp(const uint16_t* __restrict__ 
   // register.  Rows past M (columns past N) of a ragged edge tile fall
   // outside the resource and read as zero; they only enter outputs that are
   // never stored.  The scales' base index n0 K / B is exact because n0 K is a
-  // multiple of 256 * 64 >= B.
+  // multiple of 64 * 64, which every block size divides.
   uint32_t xoff[XC], woff[WC];
 #pragma unroll
   for (int i = 0; i < XC; ++i) {
@@ -601,11 +602,19 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
 // loads in the loop's order, so that its waits count those of the steady state.
 //
 // Bound by HBM for the codes up to 4 rows or so (FC1 of the 6144-wide layer at 1
-// row, 151 MB: 34 -> 27.5 us), then by the L2's rate for codes and x together,
-// since every workgroup reads its rows of x: about 10 TB/s (16 rows 45 -> 32.5
-// us, 32 rows 58 -> 37.5, 64 rows 63 -> 49).  Hence the rows per workgroup: as many
-// as leave a workgroup for each CU (rows_plan).
-constexpr uint32_t kDead = 1u << 30;        // beyond every resource here
+// row, 151 MB: 34 -> 27.5 us).  With more rows codes and x together, which every
+// workgroup reads, arrive at 5.2-5.6 TB/s (16 rows: QKV 30.6 us, FC1 36.1) and
+// 6.0-7.7 (64 rows: FC1 58.4 us on 4 waves a CU and one step ahead, QKV 43.7 on 4 and
+// two, attention output 24.5 on 8), neither HBM's rate for the codes alone nor one
+// that the L2s stop at: it falls with the waves and steps in flight, as loads whose
+// latency shows do.  x is read once a workgroup, hence the rows per workgroup: as
+// many as leave a workgroup for each CU (rows_plan).
+//
+// AS = 2: two sets of accumulators take a step's two MFMAs in turn, so that a sum is
+// two chains half as long (80 rows, N = K = 6144: error against 64 bits 2.3e-7 -> 1.2e-7,
+// 27 us either way); the plan asks for it where one chain would be longer than the
+// split kernels' (drift_limit).
+constexpr uint32_t kDead = 1u << 30;        // beyond every resource here (rows_plan)
 
 template <int XT, int MT, int NG, int W, int D, bool XL, bool KS, int AS>
 __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ x, const int8_t* __restrict__ codes,
@@ -703,7 +712,6 @@ __global__ void __launch_bounds__(64 * W) k_dqrows(const uint16_t* __restrict__ 
         xw[d][t][s] = __builtin_bit_cast(
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, (int)(xoff[t] + 2 * k0 + dead) + 16 * s, 0, 0));
   };
-  // two sets of accumulators take the MFMA steps in turn: chains half as long
   f32x4_t acc[AS][MT][NG];
 #pragma unroll
   for (int a = 0; a < AS; ++a)
