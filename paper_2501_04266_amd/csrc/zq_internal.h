@@ -111,8 +111,8 @@ using ReduceBlocksKernel = void (*)(Src, int, int64_t, uint8_t*, float*, void*, 
 QuantKernel quant_kernel(int dt, int qbits, int lgB);
 DequantKernel dequant_kernel(int dt, int qbits);
 // Groups per workgroup of the kernel of a level (its launch covers the full
-// blocks in groups of 4 wave tiles): four on large levels of two slices, else
-// one.
+// blocks in groups of 4 wave tiles): four on large levels of two slices in blocks
+// of 64 to 256, else one.
 constexpr int reduce_groups(int P, int block, bool small) {
   return !small && block >= 64 && block <= 256 && P == 2 ? 4 : 1;
 }
